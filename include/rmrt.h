@@ -27,7 +27,8 @@
  *     NCDE, usually 0.)
  *   - Every device pointer is caller-owned device memory borrowed for the
  *     lifetime of the context; the library owns only the context, its device
- *     parameter block, reduction scratch and any captured graph.
+ *     parameter block, reduction scratch, any captured graph and the second
+ *     buffer that rmrt_step describes.
  *   - Every call is ordered on the caller's hipStream_t (passed as void*;
  *     NULL = the default stream).  Only rmrt_reduce and rmrt_residual
  *     synchronise that stream, to return their FP64 results to the host.
@@ -270,6 +271,13 @@ int rmrt_set_source_fields(rmrt_ctx* ctx, const void* S, const void* F, void* st
  * Advance nsteps >= 0 time steps (eq. 2-2-3 then propagation with halfway
  * bounce-back).  nsteps > 1 replays a HIP graph of nsteps launches that is
  * captured on first use and cached per (nsteps, parity).
+ * Periodic, unforced NSE domains in the raw moments on rD3Q19 (FP32 and FP64
+ * storage) and rD3Q27 (FP32) take fours of steps as two passes of two steps
+ * each where that is faster (from about 1e6 nodes), with the bits of single
+ * steps.  An RMRT_AA domain gets a second population buffer for it on its
+ * first call of four steps or more, owned by the context until rmrt_free;
+ * without that memory (it takes at most an eighth of what is free) it steps
+ * singly.
  */
 int rmrt_step(rmrt_ctx* ctx, int nsteps, void* stream);
 
@@ -405,7 +413,8 @@ int rmrt_checkpoint_restore(rmrt_ctx* ctx, const void* src, void* stream);
  * XCD order for rD2Q9, rD2Q5 and rD3Q7 FP32/FP16; RMRT_LAUNCH_XCD_CHUNKS for
  * the other cases whose rows (n[0] x the storage element size) are not a
  * whole number of 128-byte cache lines.  Invalidates the context's cached
- * graphs.
+ * graphs.  A context whose launch shape was set here takes single steps only,
+ * in that shape; rmrt_tune chooses the shape of the single steps that remain.
  */
 #define RMRT_LAUNCH_XCD_ORDER 1
 #define RMRT_LAUNCH_PERSISTENT 2

@@ -668,4 +668,92 @@ __device__ __forceinline__ void collide(T (&t)[NS], const Coef<T>& C, const Node
   moments_inv<D, Lat<L>::dropped_mask()>(t);
 }
 
+// ----------------------------------------------------------------------------
+// The raw-moment NSE collision without sources, rounded the same in every
+// kernel: multiply-adds are fused where the source has them in one expression
+// and nowhere else.  (By default the compiler fuses across statements as the
+// code around allows, so that one collision inlined into two kernels may
+// round differently; the halvings of moments_inv are exact either way.)  The
+// domains that k_two_step serves take it in their single steps too.
+// ----------------------------------------------------------------------------
+
+// r plus the scaled raw moment n of g_eq(A, B, M).  The second moment along an
+// axis takes that axis's entry of M alone (eq. 3-5: sum c_a c_a g_eq =
+// cs2 A + M_aa).
+template <int L, int n, typename T>
+__device__ __forceinline__ T gmom_add(T r, const Coef<T>& C, T A, const T (&B)[3], const T (&Md)[3],
+                                      const T (&Mo)[3]) {
+#pragma clang fp contract(on)
+  constexpr int a = n % 3, b = (n / 3) % 3, p = n / 9;
+  constexpr int nodd = (a & 1) + (b & 1) + (p & 1);
+  if constexpr (Lat<L>::dropped(n) || nodd == 3) {
+    return r;
+  } else if constexpr (nodd == 0) {
+    constexpr bool second = a + b + p == 2;
+    r += A * C.E0[n];
+    if constexpr (!second || a == 2) r += Md[0] * C.E2[n][0];
+    if constexpr (!second || b == 2) r += Md[1] * C.E2[n][1];
+    if constexpr (Lat<L>::D == 3 && (!second || p == 2)) r += Md[2] * C.E2[n][2];
+    return r;
+  } else if constexpr (nodd == 1) {
+    constexpr int ax = (a & 1) ? 0 : ((b & 1) ? 1 : 2);
+    return r + B[ax] * C.E1[n];
+  } else {
+    constexpr int pr = (p & 1) == 0 ? 0 : ((a & 1) ? 1 : 2);  // xy, xz, yz
+    return r + Mo[pr] * C.E3[n];
+  }
+}
+
+template <int L, typename T, int NS>
+__device__ __forceinline__ void collide_nse(T (&t)[NS], const Coef<T>& C) {
+#pragma clang fp contract(on)
+  static_assert(Lat<L>::D == 3, "built for the 3D lattices");
+  moments_fwd<3, Lat<L>::absent_mask()>(t);
+  constexpr int sx = 1, sy = 3, sz = 9, sxx = 2, syy = 6, szz = 18;
+  const T eA = t[0], rho = C.rho0 + t[0];
+  const T eB[3] = {C.c[0] * t[sx], C.c[1] * t[sy], C.c[2] * t[sz]};   // rho u (eq. 2-4-2)
+  const T ir = recip(C.hl ? C.rho0 : rho);                            // u = j / rho, or j / rho0 (He-Luo)
+  const T u[3] = {eB[0] * ir, eB[1] * ir, eB[2] * ir};
+  const T eMd[3] = {eB[0] * u[0], eB[1] * u[1], eB[2] * u[2]};
+  const T eMo[3] = {eB[0] * u[1], eB[0] * u[2], eB[1] * u[2]};
+  // second-order diagonal block: t -= Sbar (t - eq)
+  {
+    const T nA = -eA, nMd[3] = {-eMd[0], -eMd[1], -eMd[2]};
+    const T n0 = gmom_add<L, sxx>(t[sxx], C, nA, eB, nMd, eMo);
+    const T n1 = gmom_add<L, syy>(t[syy], C, nA, eB, nMd, eMo);
+    const T n2 = gmom_add<L, szz>(t[szz], C, nA, eB, nMd, eMo);
+    t[sxx] -= C.Sd[0][0] * n0;
+    t[sxx] -= C.Sd[0][1] * n1;
+    t[sxx] -= C.Sd[0][2] * n2;
+    t[syy] -= C.Sd[1][0] * n0;
+    t[syy] -= C.Sd[1][1] * n1;
+    t[syy] -= C.Sd[1][2] * n2;
+    t[szz] -= C.Sd[2][0] * n0;
+    t[szz] -= C.Sd[2][1] * n1;
+    t[szz] -= C.Sd[2][2] * n2;
+  }
+  // the others: m* = (1 - r) m + g_eq(r e), rates s_off (order 2) and s_hi
+  const T r = C.s_hi, keep = T(1) - C.s_hi;
+  const T hA = r * eA;
+  const T hB[3] = {r * eB[0], r * eB[1], r * eB[2]};
+  const T hMd[3] = {r * eMd[0], r * eMd[1], r * eMd[2]};
+  const T hMo[3] = {r * eMo[0], r * eMo[1], r * eMo[2]};
+  static_for<0, NS>([&](auto n_) {
+#pragma clang fp contract(on)
+    constexpr int n = decltype(n_)::value;
+    constexpr int a = n % 3, b = (n / 3) % 3, p = n / 9, ord = a + b + p;
+    if constexpr (Lat<L>::dropped(n)) {
+      t[n] = T(0);
+    } else if constexpr (ord == 2 && n != sxx && n != syy && n != szz) {
+      constexpr int pr = (p == 0) ? 0 : ((a == 1) ? 1 : 2);
+      const T s = C.s_off[pr];
+      const T cMo[3] = {s * eMo[0], s * eMo[1], s * eMo[2]};
+      t[n] = gmom_add<L, n>((T(1) - s) * t[n], C, hA, hB, hMd, cMo);
+    } else if constexpr (ord > 2) {
+      t[n] = gmom_add<L, n>(keep * t[n], C, hA, hB, hMd, hMo);
+    }
+  });
+  moments_inv<3, Lat<L>::dropped_mask()>(t);
+}
+
 }  // namespace rmrt

@@ -325,6 +325,20 @@ __device__ __forceinline__ void local_node(const DomainDev& Dm, const Coef<T>& C
   }
 }
 
+// The two-step kernel (lbm_two_step.hpp): threads of a workgroup (one per CU) and columns per thread.  A
+// larger patch has less ring; q values per column in LDS (160 KB) and 2 q
+// loaded or waiting values per column in registers limit it: rD3Q19 FP32 1536
+// columns (117 KB, 168 registers at 12 waves; 4096 columns of 1024 threads do
+// not fit), FP64 1024 (156 KB, 256 registers at 8 waves: 347 us a step with
+// 512 columns, 303 with 1024), rD3Q27 FP32 1024 (111 KB, 128 registers).
+template <int L, int ST>
+struct TwoStep {
+  // storages and lattices with a two-step kernel
+  static constexpr bool built = (L == LAT_Q19 && (ST == ST_F32 || ST == ST_F64)) || (L == LAT_Q27 && ST == ST_F32);
+  static constexpr int kThreads = L == LAT_Q27 ? 1024 : ST == ST_F64 ? 512 : 768;
+  static constexpr int kColumns = L == LAT_Q27 ? 1 : 2;   // per thread
+};
+
 // BUF: buffer addressing (buffers below 4 GiB).  FORCE: F_NONE, F_CONST or
 // F_FIELD (the node's source terms read from the domain's field arrays).
 template <int L, int ST, int EQ, int FORCE, int BC, int PH, bool BUF>
@@ -518,6 +532,8 @@ struct NodeStep {
       T phi;
       collide<L, EQ, FORCE>(t, C, src, phi_prev, &phi);
       to_global((T*)Dm.hist)[idx] = phi;
+    } else if constexpr (TwoStep<L, ST>::built && EQ == EQ_NSE && FORCE == F_NONE) {
+      collide_nse<L>(t, C);   // the two-step kernel's arithmetic
     } else {
       collide<L, EQ, FORCE>(t, C, src);
     }
@@ -1208,7 +1224,22 @@ struct StepLaunch {
   // fused local outputs (k_step_local) when local_out is set
   void* local_out;
   int local_kind, local_f32;
+  // two steps per pass (k_two_step), two_step set: `grid` items of patches up
+  // to sweep_w columns wide; parity 1 reads buffer 1 and writes buffer 0.  With
+  // occupancy set nothing is launched: the workgroups that fit a CU and the
+  // columns of one are reported.
+  int two_step;
+  const SweepItem* sweep;
+  uint32_t sweep_w;
+  int* occupancy;
+  uint32_t* columns;
 };
+// A byte offset beyond every buffer of the two-step kernel, with room for the
+// offsets of neighbouring columns: the kernel is used for population buffers
+// and planes up to these sizes.
+constexpr uint32_t kBeyond = 0xf0000000u;
+constexpr uint32_t kTwoStepMaxBytes = 0xe0000000u, kTwoStepMaxPlane = 0x08000000u;
+
 struct AuxLaunch {
   const DomainDev* doms;
   uint32_t dom, parity;

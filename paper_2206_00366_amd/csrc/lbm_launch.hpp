@@ -2,6 +2,7 @@
 #pragma once
 
 #include "lbm_kernels.hpp"
+#include "lbm_two_step.hpp"
 
 namespace rmrt {
 
@@ -69,6 +70,12 @@ hipError_t step_f(const StepLaunch& a) {
 }
 template <int L, int ST>
 hipError_t launch_step(const StepLaunch& a) {
+  if (a.two_step) {
+    if constexpr (TwoStep<L, ST>::built)
+      return do_two_step<L, ST>(a);
+    else
+      return hipErrorInvalidValue;
+  }
   if constexpr (Lat<L>::linear) {   // rD2Q5 / rD3Q7 carry the NCDE only, always in the C = 0 form
     return (a.eq == EQ_NCDE || a.eq == EQ_NCDE_C0) ? step_f<L, ST, EQ_NCDE>(a) : hipErrorInvalidValue;
   } else {

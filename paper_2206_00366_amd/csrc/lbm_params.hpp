@@ -83,7 +83,8 @@ struct DomainDev {
   uint32_t has_solid;
   uint32_t lattice, equation, storage;
   void* fa;                 // population buffer 0
-  void* fb;                 // population buffer 1 (two-lattice pattern)
+  void* fb;                 // population buffer 1 (two-lattice pattern), or the second buffer of
+                            // the two-step path of an in-place domain (library-owned; null without)
   const uint8_t* solid;     // 1 byte per node or null
   const void* links;        // per-node link bits (uint16 for q <= 15, uint32 otherwise) or null:
                             // bit j = link x -> x + e_j hits a wall or solid; top bit = solid node
@@ -107,6 +108,12 @@ struct DomainDev {
 // One unit of persistent-kernel work: nodes [start, start + count) of a domain.
 struct Tile {
   uint32_t dom, start, count, pad;
+};
+
+// One unit of the two-step kernel's work: the inner columns [x0, x0 + cx) x
+// [y0, y0 + cy) over the planes [z0, z0 + cz).
+struct SweepItem {
+  uint32_t x0, cx, y0, cy, z0, cz;
 };
 
 }  // namespace rmrt

@@ -16,6 +16,7 @@
 
 #include "../../include/rmrt.h"
 #include "lbm_kernels.hpp"
+#include "sweep_plan.hpp"
 
 using namespace rmrt;
 
@@ -757,6 +758,14 @@ struct rmrt_ctx {
   int device = 0;              // the device current at creation
   void* sprev = nullptr;       // gamma = 0 NCDE with source fields: the previous step's source (library-owned)
   uint32_t* oob = nullptr;     // checked builds: the counter of neighbour indices out of range
+  // two steps per pass (k_two_step): the patch list, the second buffer of an
+  // in-place domain, and whether they are there (0 not asked for yet, 1 yes,
+  // -1 the domain does not qualify or the memory is not there)
+  bool launch_set = false;     // rmrt_set_launch was called: single steps of that shape only
+  int two_step = 0;
+  void* second = nullptr;
+  SweepItem* items = nullptr;
+  uint32_t nitems = 0, sweep_w = 0;
 };
 
 namespace {
@@ -838,6 +847,8 @@ void ctx_release(rmrt_ctx* c) {
   if (c->hist) (void)hipFree(c->hist);
   if (c->sprev) (void)hipFree(c->sprev);
   if (c->oob) (void)hipFree(c->oob);
+  if (c->second) (void)hipFree(c->second);
+  if (c->items) (void)hipFree(c->items);
   if (c->owns_ddoms && c->ddoms) (void)hipFree(c->ddoms);
 }
 
@@ -910,19 +921,127 @@ int launch_one_step(rmrt_ctx* c, long long step_index, hipStream_t s) {
   return RMRT_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Two steps per pass (k_two_step)
+// ---------------------------------------------------------------------------
+
+// Does the model of this context have a two-step kernel, and does its state
+// fit the kernel's addressing?  (At least four nodes per axis: a plane's two
+// neighbours, a column's two neighbours are then different ones.)
+bool two_step_model(const rmrt_ctx* c) {
+  const bool built = (c->p.lattice == RMRT_Q19 && c->p.storage != RMRT_F16DEV) ||
+                     (c->p.lattice == RMRT_Q27 && c->p.storage == RMRT_F32DEV);
+  if (!built || c->batch || step_eq(c) != EQ_NSE || step_force(c) != F_NONE || c->step_bc != 0) return false;
+  for (int a = 0; a < 3; ++a)
+    if (c->p.n[a] < 4) return false;
+  const uint64_t es = elem_size(c->p.storage);
+  return (uint64_t)lattice_q(c->p.lattice) * c->hdom.ld * es <= kTwoStepMaxBytes &&
+         (uint64_t)c->hdom.nxny * es <= kTwoStepMaxPlane;
+}
+
+StepLaunch two_step_launch(const rmrt_ctx* c) {
+  StepLaunch a;
+  std::memset(&a, 0, sizeof(a));
+  a.two_step = 1;
+  a.doms = c->ddoms + c->dom;
+  a.sweep = c->items;
+  a.grid = c->nitems;
+  a.sweep_w = c->sweep_w;
+  return a;
+}
+
+// Set up the two-step path of a context on its first call of four steps or
+// more.  A domain it does not serve, or memory that is not there, leaves the
+// single steps.
+int two_step_prepare(rmrt_ctx* c, hipStream_t s) {
+  if (c->two_step != 0) return RMRT_OK;
+  if (!two_step_model(c)) return RMRT_OK;   // asked again: source fields may be detached later
+  c->two_step = -1;
+  const int q = lattice_q(c->p.lattice), es = (int)elem_size(c->p.storage);
+  StepLaunch info = two_step_launch(c);
+  int blocks = 0;
+  uint32_t columns = 0;
+  info.occupancy = &blocks;
+  info.columns = &columns;
+  hipError_t e = dispatch_step(c->p.lattice, c->p.storage, info);
+  if (e != hipSuccess || blocks < 1) return RMRT_OK;
+  const SweepPlan plan = plan_sweep(c->hdom.nx, c->hdom.ny, c->hdom.nz, q, es, columns, (uint32_t)c->cus);
+  if (!sweep_pays(plan, c->hdom.N, q, es)) return RMRT_OK;
+  std::vector<SweepItem> items;
+  try {
+    items = sweep_items(plan, c->hdom.nx, c->hdom.ny, c->hdom.nz);
+  } catch (const std::bad_alloc&) {
+    return RMRT_OK;
+  }
+  const size_t bytes = (size_t)q * c->hdom.ld * (size_t)es;
+  if (c->p.pattern == RMRT_AA) {
+    // an in-place domain gets a second buffer, as long as that leaves most of
+    // the card's free memory to the caller
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > free_b / 8) return RMRT_OK;
+    if (hipMalloc(&c->second, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      c->second = nullptr;
+      return RMRT_OK;
+    }
+    c->hdom.fb = c->second;
+    HIP_TRY(hipMemcpyAsync(c->ddoms + c->dom, &c->hdom, sizeof(DomainDev), hipMemcpyHostToDevice, s));
+  }
+  if (hipMalloc(&c->items, sizeof(SweepItem) * items.size()) != hipSuccess) {
+    (void)hipGetLastError();
+    c->items = nullptr;
+    return RMRT_OK;
+  }
+  HIP_TRY(hipMemcpyAsync(c->items, items.data(), sizeof(SweepItem) * items.size(), hipMemcpyHostToDevice, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  c->nitems = (uint32_t)items.size();
+  c->sweep_w = plan.w;
+  c->two_step = 1;
+  return RMRT_OK;
+}
+
+// Launch n steps from step `first`: single steps, and fours of steps as two
+// passes of the two-step kernel (out to the second buffer and back, so that
+// the state ends where single steps would leave it).  An in-place domain
+// enters the two-step path in its natural layout, i.e. at an even step.
+int launch_steps(rmrt_ctx* c, int n, long long first, hipStream_t s) {
+  const bool ab = c->p.pattern == RMRT_AB;
+  const int lead = (!ab && (first & 1)) ? 1 : 0;
+  const bool two = c->two_step == 1 && !c->launch_set && two_step_model(c);
+  for (int i = 0; i < n;) {
+    if (two && i >= lead && n - i >= 4) {
+      StepLaunch a = two_step_launch(c);
+      a.stream = s;
+      const uint32_t cur = ab ? (uint32_t)((first + i) & 1) : 0u;
+      for (uint32_t h = 0; h < 2; ++h) {
+        a.parity = cur ^ h;
+        hipError_t e = dispatch_step(c->p.lattice, c->p.storage, a);
+        if (e != hipSuccess) return fail(RMRT_EHIP, "two-step launch failed: %s", hipGetErrorString(e));
+      }
+      i += 4;
+    } else {
+      int rc = launch_one_step(c, first + i, s);
+      if (rc != RMRT_OK) return rc;
+      ++i;
+    }
+  }
+  return RMRT_OK;
+}
+
 constexpr int kGraphChunk = 256;
 
 // The graph of n launches starting at step `first`, cached by (n, parity of
 // the first step): captured and instantiated on first use, and uploaded to
-// stream s when one is given (rmrt_step_prepare).
-int graph_for(rmrt_ctx* c, int n, long long first, hipGraphExec_t* out, hipStream_t upload) {
+// the stream when asked for (rmrt_step_prepare).
+int graph_for(rmrt_ctx* c, int n, long long first, hipGraphExec_t* out, hipStream_t stream, bool upload) {
   const auto key = std::make_pair(n, (int)(first & 1));
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
+    int rc = n >= 4 ? two_step_prepare(c, stream) : RMRT_OK;
+    if (rc != RMRT_OK) return rc;
     if (!c->cap) HIP_TRY(hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
-    int rc = RMRT_OK;
-    for (int i = 0; i < n && rc == RMRT_OK; ++i) rc = launch_one_step(c, first + i, c->cap);
+    rc = launch_steps(c, n, first, c->cap);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(c->cap, &g);
     if (rc != RMRT_OK) {
@@ -936,7 +1055,7 @@ int graph_for(rmrt_ctx* c, int n, long long first, hipGraphExec_t* out, hipStrea
     if (e != hipSuccess) return fail(RMRT_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
     if (c->graphs.size() >= 16) drop_graphs(c->graphs);
     it = c->graphs.emplace(key, ge).first;
-    if (upload) HIP_TRY(hipGraphUpload(ge, upload));
+    if (upload) HIP_TRY(hipGraphUpload(ge, stream));
   }
   *out = it->second;
   return RMRT_OK;
@@ -945,7 +1064,7 @@ int graph_for(rmrt_ctx* c, int n, long long first, hipGraphExec_t* out, hipStrea
 // steps n launches as a cached graph keyed by (n, parity of the first step)
 int run_graph(rmrt_ctx* c, int n, hipStream_t s) {
   hipGraphExec_t ge = nullptr;
-  int rc = graph_for(c, n, c->steps, &ge, nullptr);
+  int rc = graph_for(c, n, c->steps, &ge, s, false);
   if (rc != RMRT_OK) return rc;
   HIP_TRY(hipGraphLaunch(ge, s));
   c->steps += n;
@@ -959,13 +1078,13 @@ int prepare_graphs(rmrt_ctx* c, int n, long long first, hipStream_t s, long long
   hipGraphExec_t ge = nullptr;
   int left = n;
   while (left >= kGraphChunk) {
-    int rc = graph_for(c, kGraphChunk, first, &ge, s);
+    int rc = graph_for(c, kGraphChunk, first, &ge, s, true);
     if (rc != RMRT_OK) return rc;
     first += kGraphChunk;
     left -= kGraphChunk;
   }
   if (left > 1) {
-    int rc = graph_for(c, left, first, &ge, s);
+    int rc = graph_for(c, left, first, &ge, s, true);
     if (rc != RMRT_OK) return rc;
   }
   *after = first + left;
@@ -1504,6 +1623,7 @@ int rmrt_set_launch(rmrt_ctx* c, int blocks_per_cu, int flags) {
     return fail(RMRT_EINVAL, "a residency cap of 1 workgroup per CU is not supported (use >= 2)");
   c->blocks_per_cu = blocks_per_cu;
   c->flags = (uint32_t)flags;
+  c->launch_set = true;
   drop_graphs(c->graphs);
   return RMRT_OK;
 }
@@ -1553,7 +1673,9 @@ int rmrt_tune(rmrt_ctx* c, int steps, void* stream, int* blocks_per_cu) {
     }
   }
   if (blocks_per_cu) *blocks_per_cu = best;
-  return rmrt_set_launch(c, best, best_flags);
+  const int rc = rmrt_set_launch(c, best, best_flags);
+  c->launch_set = false;   // the shape of the single steps; fours of steps stay on the two-step path
+  return rc;
 }
 
 int rmrt_free(rmrt_ctx* c) {
