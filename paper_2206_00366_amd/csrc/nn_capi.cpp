@@ -12,7 +12,7 @@ namespace nn {
 hipError_t launch_conv(const uint16_t*, const uint16_t*, const float*, float*, uint16_t*, const float*, int, int, int,
                        int, int, int, int, hipStream_t);
 hipError_t launch_flip(const uint16_t*, uint16_t*, int, int, hipStream_t);
-size_t wgrad_partial_floats(long, int, int, int);
+size_t wgrad_partial_floats(int, int, int, int, int);
 hipError_t launch_wgrad(const uint16_t*, const uint16_t*, int, int, int, int, int, int, float*, float*, float*, size_t,
                         hipStream_t);
 hipError_t launch_mse(const float*, int, const float*, const float*, long, int, uint16_t*, double*, float*, double*,
@@ -71,15 +71,15 @@ int rmrt_nn_flip_weights(const void* w, void* wt, int Cout, int Cin, void* strea
 }
 
 size_t rmrt_nn_wgrad_scratch_floats(int B, int H, int W, int Cin, int Cout) {
-  const size_t a = wgrad_partial_floats((long)B * H * W, Cin, Cout, 1024);
-  const size_t b = (size_t)1024 * Cout;
-  return a > b ? a : b;
+  if (B < 1 || H < 1 || W < 1 || !ch_ok(Cin) || !ch_ok(Cout)) return 0;
+  return wgrad_partial_floats(B, H, W, Cin, Cout);
 }
 
 int rmrt_nn_conv_backward_weight(const void* x, const void* dy, int B, int H, int W, int Cin, int Cout, int dil,
                                  float* dw, float* db, float* scratch, size_t scratch_floats, void* stream) {
   if (!x || !dy || !dw || !scratch) return nn_fail(RMRT_EINVAL, "NULL pointer");
   if (!ch_ok(Cin) || !ch_ok(Cout)) return nn_fail(RMRT_EUNSUPPORTED, "channels must be 16 or 32");
+  if (B < 1 || H < 1 || W < 1) return nn_fail(RMRT_EINVAL, "bad sizes");
   if (scratch_floats < rmrt_nn_wgrad_scratch_floats(B, H, W, Cin, Cout))
     return nn_fail(RMRT_EINVAL, "scratch too small");
   return hip_rc(launch_wgrad((const uint16_t*)x, (const uint16_t*)dy, B, H, W, Cin, Cout, dil, dw, db, scratch,
