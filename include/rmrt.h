@@ -333,7 +333,7 @@ int rmrt_local_gradients(rmrt_ctx* ctx, int kind, void* out, int out_dtype, void
  * otherwise), so the second non-equilibrium moment carries the FP32 rounding
  * of the collision.  Costs one step plus the output writes (no second read of
  * the state).  Advances the context by one step (one workgroup per tile, the
- * context's residency cap and tile order, 64-bit addressing; no health check).  RMRT_EINVAL
+ * context's residency cap, tile order and addressing; no health check).  RMRT_EINVAL
  * for a domain of a batch.  For the coupling loops of eq. 4-28 (a strain-rate
  * dependent viscosity) and eq. 4-13.
  */

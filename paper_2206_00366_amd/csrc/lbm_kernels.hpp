@@ -720,17 +720,21 @@ __global__ void __launch_bounds__(256)
 // One step of a single domain fused with its local outputs (stress / strain
 // rate or grad phi of the state the step starts from, computed from the loaded
 // deviations in the step's working precision).  One workgroup per tile, one
-// node per thread, 64-bit addressing.
-template <int L, int ST, int EQ, int FORCE, int BC, int PH>
+// node per thread; addressing and tile order as in k_step.  Bound by HBM (the
+// step's bytes and the outputs); rD3Q27 FP32 223 x 116 x 100 with walls and
+// force, even / odd: 113 / 131 us with 64-bit addressing and without the XCD
+// chunks, 108 / 120 us now.
+template <int L, int ST, int EQ, int FORCE, int BC, int PH, bool BUF>
 __global__ void __launch_bounds__(256)
     k_step_local(const DomainDev* __restrict__ doms, uint32_t tile_nodes, uint32_t parity, void* out, int kind,
-                 int out_f32, int alternate) {
+                 int out_f32, uint32_t flags) {
   using SS = Store<ST>;
   using S = typename SS::S;
   using T = typename SS::T;
   const DomainDev& Dm = doms[0];
   const Coef<T>& C = coef<T>(Dm);
-  const uint32_t tile = (alternate && (parity & 1u)) ? gridDim.x - 1u - blockIdx.x : blockIdx.x;
+  uint32_t tile = (PH != PH_AA_EVEN && (flags & STEP_XCD_CHUNKS)) ? xcd_chunk_tile(blockIdx.x, gridDim.x) : blockIdx.x;
+  if ((flags & STEP_ALTERNATE_ORDER) && (parity & 1u)) tile = gridDim.x - 1u - tile;
   const uint32_t N = Dm.N, start = tile * tile_nodes;
   if (start >= N) return;
   const uint32_t count = (N - start < tile_nodes) ? N - start : tile_nodes;
@@ -738,12 +742,14 @@ __global__ void __launch_bounds__(256)
   gmem<S>* fb = to_global((S*)Dm.fb);
   gmem<S>* fin = (PH == PH_AB && parity) ? fb : fa;
   gmem<S>* fout = (PH == PH_AB) ? (parity ? fa : fb) : fa;
-  using NSp = NodeStep<L, ST, EQ, FORCE, BC, PH, false>;
+  using NSp = NodeStep<L, ST, EQ, FORCE, BC, PH, BUF>;
+  const auto rin = StreamRes<BUF>::template make<Lat<L>::Q>((const gmem<S>*)fin, BUF ? Dm.ld : 0u);
+  const auto rout = StreamRes<BUF>::template make<Lat<L>::Q>((const gmem<S>*)fout, BUF ? Dm.ld : 0u);
   for (uint32_t i = threadIdx.x; i < count; i += blockDim.x) {
     NSp a;
-    a.load(Dm, C, fin, 0, start + i, true);
+    a.load(Dm, C, fin, rin, start + i, true);
     a.local_out(Dm, C, out, kind, out_f32);
-    a.finish(Dm, C, fout, 0);
+    a.finish(Dm, C, fout, rout);
   }
 }
 

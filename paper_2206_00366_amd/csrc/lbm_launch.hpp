@@ -29,9 +29,12 @@ hipError_t do_step(const StepLaunch& a) {
     if constexpr (F == F_FIELD || EQ == EQ_NSE_BASIS) {
       return hipErrorInvalidValue;   // local outputs: raw-moment model, constant sources (host-checked)
     } else {
-      hipLaunchKernelGGL((k_step_local<L, ST, EQ, F, BC, PH>), dim3(a.ntiles), dim3(a.block), a.lds_bytes,
-                         a.stream, a.doms, a.tile_nodes, a.parity, a.local_out, a.local_kind, a.local_f32,
-                         (int)((a.flags & STEP_ALTERNATE_ORDER) != 0));
+      if (a.flags & STEP_BUFFER_OFFSETS)
+        hipLaunchKernelGGL((k_step_local<L, ST, EQ, F, BC, PH, true>), dim3(a.ntiles), dim3(a.block), a.lds_bytes,
+                           a.stream, a.doms, a.tile_nodes, a.parity, a.local_out, a.local_kind, a.local_f32, a.flags);
+      else
+        hipLaunchKernelGGL((k_step_local<L, ST, EQ, F, BC, PH, false>), dim3(a.ntiles), dim3(a.block), a.lds_bytes,
+                           a.stream, a.doms, a.tile_nodes, a.parity, a.local_out, a.local_kind, a.local_f32, a.flags);
       return hipGetLastError();
     }
   }

@@ -1428,7 +1428,8 @@ int rmrt_step_local(rmrt_ctx* c, int kind, void* out, int out_dtype, void* strea
   a.tiles = nullptr;
   a.tile_nodes = 256;
   a.ntiles = (c->hdom.N + a.tile_nodes - 1) / a.tile_nodes;
-  a.flags = c->flags & STEP_ALTERNATE_ORDER;
+  a.flags = c->flags & (STEP_ALTERNATE_ORDER | STEP_XCD_CHUNKS | STEP_BUFFER_OFFSETS);
+  if (!buffer_offsets_apply(c)) a.flags &= ~STEP_BUFFER_OFFSETS;
   a.parity = (uint32_t)(c->steps & 1);
   a.eq = step_eq(c);
   a.force = step_force(c);
