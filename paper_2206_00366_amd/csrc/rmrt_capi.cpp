@@ -1955,6 +1955,24 @@ int batch_build_tiles(rmrt_batch* b, int cfg, hipStream_t s) {
   return RMRT_OK;
 }
 
+// The tile configuration a batch starts with: 256-node tiles with the residency
+// cap its domains would have as single ones (default_launch).  Under the cap of
+// 2 that every batch started with before, 16 rD2Q9 FP32 obstacle channels of
+// 512 x 256 took 52 us a step (uncapped 27) and 24 rD3Q27 FP32 channels of
+// 32 .. 160 nodes per axis 970 us (cap of 4: 890).
+int default_batch_config(const rmrt_params* params, const rmrt_batch* b) {
+  rmrt_params p = params[0];
+  for (int a = 0; a < 3; ++a) p.force[a] = b->force ? 1.0 : 0.0;   // forced when any domain is
+  int cap = 0;
+  uint32_t flags = 0;
+  default_launch(p, b->bc != 0, cap, flags);
+  for (int k = 0; k < kNumTileShapes; ++k) {
+    const TileConfig& t = kTileShapes[k];
+    if (!t.persistent && t.nodes_per_thread == 1 && t.blocks_per_cu == cap) return k;
+  }
+  return 1;
+}
+
 int batch_launch(rmrt_batch* b, long long step_index, hipStream_t s, size_t group) {
   const TileConfig& tc = kTileShapes[b->cfg];
   StepLaunch a;
@@ -2148,7 +2166,7 @@ int rmrt_batch_create(rmrt_batch** out, int nd, const rmrt_params* params, void*
     delete b;
     return fail(RMRT_EHIP, "param upload: %s", hipGetErrorString(e));
   }
-  int rc = batch_build_tiles(b, 1, s);
+  int rc = batch_build_tiles(b, default_batch_config(params, b), s);
   for (int d = 0; d < nd && rc == RMRT_OK; ++d)
     if (b->ctxs[d]->links) rc = build_links(b->ctxs[d], s);
   for (int d = 0; d < nd && rc == RMRT_OK; ++d) rc = launch_init_fields(b->ctxs[d], nullptr, nullptr, 0, s);
