@@ -277,7 +277,10 @@ int rmrt_set_source_fields(rmrt_ctx* ctx, const void* S, const void* F, void* st
  * steps.  An RMRT_AA domain gets a second population buffer for it on its
  * first call of four steps or more, owned by the context until rmrt_free;
  * without that memory (it takes at most an eighth of what is free) it steps
- * singly.
+ * singly.  rD2Q9 domains and batches (raw-moment NSE, or NCDE without c_zero;
+ * FP32, or FP64 without force and source; walls on both of two opposite faces
+ * or none; solid masks) take four steps or more as passes of up to four steps
+ * each on the same terms.
  */
 int rmrt_step(rmrt_ctx* ctx, int nsteps, void* stream);
 
@@ -413,7 +416,8 @@ int rmrt_checkpoint_restore(rmrt_ctx* ctx, const void* src, void* stream);
  * XCD order for rD2Q9, rD2Q5 and rD3Q7 FP32/FP16; RMRT_LAUNCH_XCD_CHUNKS for
  * the other cases whose rows (n[0] x the storage element size) are not a
  * whole number of 128-byte cache lines.  Invalidates the context's cached
- * graphs.  A context whose launch shape was set here takes single steps only,
+ * graphs.  A context (or batch: rmrt_batch_set_config, _set_group_bytes,
+ * _set_xcd_chunks) whose launch shape was set here takes single steps only,
  * in that shape; rmrt_tune chooses the shape of the single steps that remain.
  */
 #define RMRT_LAUNCH_XCD_ORDER 1

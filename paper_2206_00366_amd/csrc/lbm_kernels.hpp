@@ -339,6 +339,15 @@ struct TwoStep {
   static constexpr int kColumns = L == LAT_Q27 ? 1 : 2;   // per thread
 };
 
+// Several steps per pass on rD2Q9 (lbm_tile_steps.hpp): the ring and so the most
+// steps of a pass, nodes per thread, threads of a workgroup (kTileThreads; FP64
+// also with twice as many) and workgroups that run on a CU (9 values per node
+// in LDS: 74 KB, or 147 KB).
+constexpr uint32_t kTileRing = 4, kTileNodes = 4;
+constexpr uint32_t kTileThreads(int st) { return st == ST_F64 ? 256u : 512u; }
+constexpr bool tile_steps_built(int st) { return st == ST_F32 || st == ST_F64; }
+constexpr bool tile_force_built(int st, int force) { return force == F_NONE || (force == F_CONST && st == ST_F32); }
+
 // BUF: buffer addressing (buffers below 4 GiB).  FORCE: F_NONE, F_CONST or
 // F_FIELD (the node's source terms read from the domain's field arrays).
 template <int L, int ST, int EQ, int FORCE, int BC, int PH, bool BUF>
@@ -782,7 +791,7 @@ __device__ __forceinline__ typename Store<ST>::S* current_buffer(const DomainDev
 
 // Gather the deviations d_j of node idx (paper order, FP64).
 template <int L, int ST, int BC, bool SWAPPED>
-__device__ __forceinline__ void gather64(const DomainDev& Dm, const typename Store<ST>::S* f,
+__device__ __forceinline__ void gather64(const DomainDev& Dm, const gmem<typename Store<ST>::S>* f,
                                          uint32_t idx, double (&d)[Lat<L>::Q]) {
   constexpr int D = Lat<L>::D;
   Geo<D> g;
@@ -841,7 +850,7 @@ __device__ __forceinline__ HalfSrc half_sources(const DomainDev& Dm, uint32_t id
 
 // rho (or phi) and u of node idx (eq. 2-4-1 / eq. 2-4-2)
 template <int L, int ST, int EQ, int BC, bool SWAPPED>
-__device__ __forceinline__ void macro_node(const DomainDev& Dm, const typename Store<ST>::S* f,
+__device__ __forceinline__ void macro_node(const DomainDev& Dm, const gmem<typename Store<ST>::S>* f,
                                            uint32_t idx, double& rho, double (&u)[3],
                                            double& drho_out) {
   double d[Lat<L>::Q];
@@ -869,7 +878,7 @@ __global__ void __launch_bounds__(256)
     k_moments(const DomainDev* __restrict__ doms, uint32_t dom, uint32_t parity, int ab, void* rho_out,
               void* u_out, int out_f32) {
   const DomainDev& Dm = doms[dom];
-  const auto* f = current_buffer<ST>(Dm, parity, ab);
+  const auto* f = to_global(current_buffer<ST>(Dm, parity, ab));
   constexpr int D = Lat<L>::D;
   const uint32_t N = Dm.N;
   for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < N; idx += gridDim.x * blockDim.x) {
@@ -897,7 +906,7 @@ __global__ void __launch_bounds__(256)
     k_populations(const DomainDev* __restrict__ doms, uint32_t dom, uint32_t parity, int ab,
                   double* out) {
   const DomainDev& Dm = doms[dom];
-  const auto* f = current_buffer<ST>(Dm, parity, ab);
+  const auto* f = to_global(current_buffer<ST>(Dm, parity, ab));
   const uint32_t N = Dm.N;
   for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < N; idx += gridDim.x * blockDim.x) {
     if (BC == 1 && Dm.has_solid && Dm.solid[idx]) {
@@ -933,7 +942,7 @@ __global__ void __launch_bounds__(256)
             int out_f32) {
   const DomainDev& Dm = doms[dom];
   const Coef<double>& C = Dm.cd;
-  const auto* f = current_buffer<ST>(Dm, parity, ab);
+  const auto* f = to_global(current_buffer<ST>(Dm, parity, ab));
   constexpr int D = Lat<L>::D;
   constexpr int NC = (EQ == EQ_NSE) ? D * (D + 1) / 2 : D;
   const uint32_t N = Dm.N;
@@ -985,7 +994,7 @@ __global__ void __launch_bounds__(256)
     k_reduce(const DomainDev* __restrict__ doms, uint32_t dom, uint32_t parity, int ab,
              double* partials) {
   const DomainDev& Dm = doms[dom];
-  const auto* f = current_buffer<ST>(Dm, parity, ab);
+  const auto* f = to_global(current_buffer<ST>(Dm, parity, ab));
   const uint32_t N = Dm.N;
   double acc[5] = {0, 0, 0, 0, 0};
   for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < N; idx += gridDim.x * blockDim.x) {
@@ -1006,18 +1015,45 @@ __global__ void __launch_bounds__(256)
   block_reduce_store<5>(acc, partials);
 }
 
+// Sum of nb x K partials in a fixed order (deterministic); the result is
+// valid in thread 0 of a single 256-thread workgroup.  (The last 256 sums go
+// through a tree; one thread adding them took most of the 12 us that a
+// reduction of five sums cost, now 4 us.)
+template <int K>
+__device__ __forceinline__ void sum_partials(const double* __restrict__ partials, uint32_t nb, double (&res)[K]) {
+  __shared__ double sh[K][4];
+  const gmem<double>* part = to_global(partials);
+  for (int k = 0; k < K; ++k) res[k] = 0.0;
+  for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x)
+    for (int k = 0; k < K; ++k) res[k] += part[(size_t)b * K + k];
+  for (int k = 0; k < K; ++k) {
+    for (int o = 32; o > 0; o >>= 1) res[k] += __shfl_xor(res[k], o, 64);
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = res[k];
+  }
+  __syncthreads();
+  for (int k = 0; k < K; ++k) res[k] = (sh[k][0] + sh[k][1]) + (sh[k][2] + sh[k][3]);
+}
+
+template <int K>
+__global__ void k_reduce_final(const double* __restrict__ partials, uint32_t nb, double* out) {
+  double res[K];
+  sum_partials<K>(partials, nb, res);
+  if (threadIdx.x == 0)
+    for (int k = 0; k < K; ++k) out[k] = res[k];
+}
+
+
 // steady residual partials: [sum |u - u_prev|^2, sum |u|^2]; stores u into prev
-// (NCDE: phi instead of u)
+// (NCDE: phi instead of u).  Workgroup `block` of `nblocks` of one domain.
 template <int L, int ST, int EQ, int BC, bool SWAPPED>
-__global__ void __launch_bounds__(256)
-    k_residual(const DomainDev* __restrict__ doms, uint32_t dom, uint32_t parity, int ab, double* prev,
-               int have_prev, double* partials) {
-  const DomainDev& Dm = doms[dom];
-  const auto* f = current_buffer<ST>(Dm, parity, ab);
+__device__ __forceinline__ void residual_part(const DomainDev& Dm, uint32_t parity, int ab, double* prev_, int have_prev,
+                                              uint32_t block, uint32_t nblocks, double* partials) {
+  const auto* f = to_global(current_buffer<ST>(Dm, parity, ab));
   const uint32_t N = Dm.N;
+  gmem<double>* prev = to_global(prev_);
   constexpr int K = (EQ == EQ_NSE) ? Lat<L>::D : 1;
   double acc[2] = {0, 0};
-  for (uint32_t idx = blockIdx.x * blockDim.x + threadIdx.x; idx < N; idx += gridDim.x * blockDim.x) {
+  for (uint32_t idx = block * blockDim.x + threadIdx.x; idx < N; idx += nblocks * blockDim.x) {
     if (BC == 1 && Dm.has_solid && Dm.solid[idx]) continue;
     double rho, u[3], drho;
     macro_node<L, ST, EQ, BC, SWAPPED>(Dm, f, idx, rho, u, drho);
@@ -1032,35 +1068,33 @@ __global__ void __launch_bounds__(256)
   }
   block_reduce_store<2>(acc, partials);
 }
-
-// Sum of nb x K partials in a fixed order (deterministic); the result is
-// valid in thread 0 of a single 256-thread workgroup.
-template <int K>
-__device__ __forceinline__ void sum_partials(const double* __restrict__ partials, uint32_t nb, double (&res)[K]) {
-  __shared__ double sh[K][256];
-  double v[K];
-  for (int k = 0; k < K; ++k) v[k] = 0.0;
-  for (uint32_t b = threadIdx.x; b < nb; b += blockDim.x)
-    for (int k = 0; k < K; ++k) v[k] += partials[(size_t)b * K + k];
-  for (int k = 0; k < K; ++k) sh[k][threadIdx.x] = v[k];
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int k = 0; k < K; ++k) {
-      double s = 0.0;
-      for (uint32_t t = 0; t < blockDim.x; ++t) s += sh[k][t];
-      res[k] = s;
-    }
-  }
+template <int L, int ST, int EQ, int BC, bool SWAPPED>
+__global__ void __launch_bounds__(256)
+    k_residual(const DomainDev* __restrict__ doms, uint32_t dom, uint32_t parity, int ab, double* prev,
+               int have_prev, double* partials) {
+  residual_part<L, ST, EQ, BC, SWAPPED>(doms[dom], parity, ab, prev, have_prev, blockIdx.x, gridDim.x, partials);
 }
-
+// The same for every domain of a batch in one launch: workgroup b takes part
+// blocks[b].start of blocks[b].count of domain blocks[b].dom, with the parts
+// and so the sums of one k_residual per domain (16 domains of 512 x 256: 90 us
+// of launches of 5.6 us each, now 10 us).
+template <int L, int ST, int EQ, int BC, bool SWAPPED>
+__global__ void __launch_bounds__(256)
+    k_residual_batch(const DomainDev* __restrict__ doms, const Tile* __restrict__ blocks,
+                     const ResidualState* __restrict__ states, uint32_t parity, int ab, double* partials) {
+  const Tile t = blocks[blockIdx.x];
+  const ResidualState s = states[t.dom];
+  residual_part<L, ST, EQ, BC, SWAPPED>(doms[t.dom], parity, ab, s.prev, (int)s.have_prev, t.start, t.count, partials);
+}
+// final sums of a batch: domain blockIdx.x, its partials from first_block on
 template <int K>
-__global__ void k_reduce_final(const double* __restrict__ partials, uint32_t nb, double* out) {
+__global__ void k_final_batch(const double* __restrict__ partials, const ResidualState* __restrict__ states, double* out) {
+  const ResidualState s = states[blockIdx.x];
   double res[K];
-  sum_partials<K>(partials, nb, res);
+  sum_partials<K>(partials + (size_t)s.first_block * K, s.nblocks, res);
   if (threadIdx.x == 0)
-    for (int k = 0; k < K; ++k) out[k] = res[k];
+    for (int k = 0; k < K; ++k) out[(size_t)blockIdx.x * K + k] = res[k];
 }
-
 
 // ----------------------------------------------------------------------------
 // Initialisation: fbar = g_eq(A, B, M) in velocity space (eq. 3-3) with
@@ -1239,6 +1273,10 @@ struct StepLaunch {
   uint32_t sweep_w;
   int* occupancy;
   uint32_t* columns;
+  // two_step 2: pass_steps steps per pass over `grid` tiles up to sweep_w wide
+  // (k_tile_steps with `block` threads), parity as above
+  const TileItem* tile_items;
+  uint32_t pass_steps;
 };
 // A byte offset beyond every buffer of the two-step kernel, with room for the
 // offsets of neighbouring columns: the kernel is used for population buffers
@@ -1259,6 +1297,11 @@ struct AuxLaunch {
   const double* in1;
   int flag;
   int kind;   // k_local: GRAD_*
+  // k_residual_batch when blocks is set: the parts of every domain and their
+  // states, `grid` parts, partials to out0, final sums of nstates to out1
+  const Tile* blocks;
+  const ResidualState* states;
+  unsigned nstates;
 };
 
 template <int L, int ST>

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "lbm_kernels.hpp"
+#include "lbm_tile_steps.hpp"
 #include "lbm_two_step.hpp"
 
 namespace rmrt {
@@ -73,6 +74,12 @@ hipError_t step_f(const StepLaunch& a) {
 }
 template <int L, int ST>
 hipError_t launch_step(const StepLaunch& a) {
+  if (a.two_step == 2) {
+    if constexpr (L == LAT_Q9 && tile_steps_built(ST))
+      return launch_tile_steps<ST>(a);
+    else
+      return hipErrorInvalidValue;
+  }
   if (a.two_step) {
     if constexpr (TwoStep<L, ST>::built)
       return do_two_step<L, ST>(a);
@@ -128,7 +135,23 @@ hipError_t launch_reduce(const AuxLaunch& a) {
 }
 
 template <int L, int ST>
+hipError_t launch_residual_parts(const AuxLaunch& a) {
+#define K_RESB(EQ, BC, SW)                                                                                    \
+  hipLaunchKernelGGL((k_residual_batch<L, ST, EQ, BC, SW>), dim3(a.grid), dim3(a.block), 0, a.stream, a.doms, \
+                     a.blocks, a.states, a.parity, a.ab, (double*)a.out0)
+  RMRT_AUX_DISPATCH(K_RESB)
+#undef K_RESB
+}
+
+template <int L, int ST>
 hipError_t launch_residual(const AuxLaunch& a) {
+  if (a.blocks) {
+    hipError_t e = launch_residual_parts<L, ST>(a);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_final_batch<2>), dim3(a.nstates), dim3(256), 0, a.stream, (const double*)a.out0, a.states,
+                       (double*)a.out1);
+    return hipGetLastError();
+  }
 #define K_RES(EQ, BC, SW)                                                                           \
   hipLaunchKernelGGL((k_residual<L, ST, EQ, BC, SW>), dim3(a.grid), dim3(a.block), 0, a.stream, a.doms, \
                      a.dom, a.parity, a.ab, (double*)a.out1, a.flag, (double*)a.out0)

@@ -110,6 +110,19 @@ struct Tile {
   uint32_t dom, start, count, pad;
 };
 
+// A domain's part in the residual of a batch: the previous velocities, whether
+// they are set, and its workgroups in the launch.
+struct ResidualState {
+  double* prev;
+  uint32_t have_prev, first_block, nblocks, pad;
+};
+
+// One unit of the tile kernel's work: the inner nodes [x0, x0 + cx) x
+// [y0, y0 + cy) of a 2D domain.
+struct TileItem {
+  uint32_t dom, x0, cx, y0, cy;
+};
+
 // One unit of the two-step kernel's work: the inner columns [x0, x0 + cx) x
 // [y0, y0 + cy) over the planes [z0, z0 + cz).
 struct SweepItem {

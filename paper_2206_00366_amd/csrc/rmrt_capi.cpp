@@ -765,7 +765,8 @@ struct rmrt_ctx {
   int two_step = 0;
   void* second = nullptr;
   SweepItem* items = nullptr;
-  uint32_t nitems = 0, sweep_w = 0;
+  TileItem* tile_items = nullptr;   // rD2Q9: several steps per pass (k_tile_steps) instead
+  uint32_t nitems = 0, sweep_w = 0, tile_threads = 0;
 };
 
 namespace {
@@ -849,6 +850,7 @@ void ctx_release(rmrt_ctx* c) {
   if (c->oob) (void)hipFree(c->oob);
   if (c->second) (void)hipFree(c->second);
   if (c->items) (void)hipFree(c->items);
+  if (c->tile_items) (void)hipFree(c->tile_items);
   if (c->owns_ddoms && c->ddoms) (void)hipFree(c->ddoms);
 }
 
@@ -939,6 +941,86 @@ bool two_step_model(const rmrt_ctx* c) {
          (uint64_t)c->hdom.nxny * es <= kTwoStepMaxPlane;
 }
 
+// The same for the tile kernel (rD2Q9; equation and source mode of the launch,
+// which for a domain of a batch are the batch's).
+bool tile_model(const rmrt_ctx* c, int eq, int force) {
+  if (c->p.lattice != RMRT_Q9 || c->p.storage == RMRT_F16DEV || !buffer_offsets_apply(c)) return false;
+  if ((eq != EQ_NSE && eq != EQ_NCDE) || !tile_force_built(c->p.storage, force)) return false;
+  // a wall on one of two opposite faces only: the populations that cross the
+  // other face are written twice per step, so the order of the writes matters
+  const unsigned w = c->hdom.walls;
+  if ((w & 5u) != ((w >> 1) & 5u)) return false;
+  return c->p.n[0] >= 8 && c->p.n[1] >= 8;
+}
+
+// Tiles of the given domains, or none where single steps are faster: of the
+// workgroups and of the tile sizes of 1 .. 4 nodes per thread the ones with the
+// shortest pass.
+std::vector<TileItem> plan_tiles(const std::vector<rmrt_ctx*>& doms, uint32_t cus, uint32_t* width, uint32_t* threads) {
+  const int es = (int)elem_size(doms[0]->p.storage);
+  double best_us = 1e300;
+  uint32_t best = 0;
+  uint64_t nodes = 0;
+  for (const rmrt_ctx* c : doms) nodes += c->hdom.N;
+  for (uint32_t twice = 0; twice < (es == 8 ? 2u : 1u); ++twice) {
+    const uint32_t nt = kTileThreads(doms[0]->p.storage) << twice, slots = cus * (2u - twice);
+    for (uint32_t blocks = 1; blocks <= kTileNodes; ++blocks) {
+      uint64_t tiles = 0;
+      bool fits = true;
+      for (const rmrt_ctx* c : doms) {
+        const TileSplit t = split_tiles(c->hdom.nx, c->hdom.ny, blocks * nt, kTileRing);
+        fits = fits && t.cx > 0;
+        tiles += t.tiles;
+      }
+      if (!fits) continue;
+      const double us = tile_pass_us(tiles, blocks, slots, es, nt, kTileRing);
+      if (us < best_us) {
+        best_us = us;
+        best = blocks * nt;
+        *threads = nt;
+      }
+    }
+  }
+  std::vector<TileItem> items;
+  *width = 0;
+  if (best == 0 || !tiles_pay(best_us, nodes, es, kTileRing)) return items;
+  for (size_t d = 0; d < doms.size(); ++d) {
+    const uint32_t nx = doms[d]->hdom.nx, ny = doms[d]->hdom.ny;
+    const TileSplit t = split_tiles(nx, ny, best, kTileRing);
+    *width = std::max(*width, t.w);
+    for (uint32_t y = 0; y < ny; y += t.cy)
+      for (uint32_t x = 0; x < nx; x += t.cx)
+        items.push_back(TileItem{(uint32_t)d, x, std::min(t.cx, nx - x), y, std::min(t.cy, ny - y)});
+  }
+  // a contiguous run of tiles for each XCD, as in sweep_items
+  const size_t n = items.size(), q8 = n / 8, rem = n % 8;
+  std::vector<TileItem> out(n);
+  for (size_t k = 0; k < n; ++k) out[k] = items[(k % 8) * q8 + std::min(k % 8, rem) + k / 8];
+  return out;
+}
+
+// Memory for the second buffers of in-place domains: only where it leaves most
+// of the card's free memory to the caller.  Null otherwise.
+void* second_buffer(size_t bytes) {
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > free_b / 8) return nullptr;
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  return p;
+}
+
+// Steps of pass k of the passes that take m (even) steps between them: an even
+// number of passes of at most kTileRing steps, so that the state ends in the
+// buffer where single steps would leave it.
+int tile_passes(int m) { return 2 * ((m + 2 * (int)kTileRing - 1) / (2 * (int)kTileRing)); }
+int tile_pass_steps(int m, int k) {
+  const int passes = tile_passes(m);
+  return m / passes + (k < m % passes ? 1 : 0);
+}
+
 StepLaunch two_step_launch(const rmrt_ctx* c) {
   StepLaunch a;
   std::memset(&a, 0, sizeof(a));
@@ -950,11 +1032,53 @@ StepLaunch two_step_launch(const rmrt_ctx* c) {
   return a;
 }
 
+// The tile path of an rD2Q9 context, set up on its first call of four steps or more.
+int tile_prepare(rmrt_ctx* c, hipStream_t s) {
+  if (c->batch || !tile_model(c, step_eq(c), step_force(c))) return RMRT_OK;
+  c->two_step = -1;
+  std::vector<TileItem> items;
+  try {
+    items = plan_tiles({c}, (uint32_t)c->cus, &c->sweep_w, &c->tile_threads);
+  } catch (const std::bad_alloc&) {
+    return RMRT_OK;
+  }
+  if (items.empty()) return RMRT_OK;
+  if (c->p.pattern == RMRT_AA) {
+    c->second = second_buffer((size_t)9 * c->hdom.ld * elem_size(c->p.storage));
+    if (!c->second) return RMRT_OK;
+    c->hdom.fb = c->second;
+    HIP_TRY(hipMemcpyAsync(c->ddoms + c->dom, &c->hdom, sizeof(DomainDev), hipMemcpyHostToDevice, s));
+  }
+  if (hipMalloc(&c->tile_items, sizeof(TileItem) * items.size()) != hipSuccess) {
+    (void)hipGetLastError();
+    c->tile_items = nullptr;
+    return RMRT_OK;
+  }
+  HIP_TRY(hipMemcpyAsync(c->tile_items, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  c->nitems = (uint32_t)items.size();
+  c->two_step = 2;
+  return RMRT_OK;
+}
+
+// The passes of m (even) steps from step `first`.
+int launch_tile_passes(StepLaunch a, int lattice, int storage, bool ab, int m, long long first) {
+  const uint32_t cur = ab ? (uint32_t)(first & 1) : 0u;
+  for (int k = 0; k < tile_passes(m); ++k) {
+    a.parity = cur ^ (uint32_t)(k & 1);
+    a.pass_steps = (uint32_t)tile_pass_steps(m, k);
+    hipError_t e = dispatch_step(lattice, storage, a);
+    if (e != hipSuccess) return fail(RMRT_EHIP, "tile pass launch failed: %s", hipGetErrorString(e));
+  }
+  return RMRT_OK;
+}
+
 // Set up the two-step path of a context on its first call of four steps or
 // more.  A domain it does not serve, or memory that is not there, leaves the
 // single steps.
 int two_step_prepare(rmrt_ctx* c, hipStream_t s) {
   if (c->two_step != 0) return RMRT_OK;
+  if (c->p.lattice == RMRT_Q9) return tile_prepare(c, s);
   if (!two_step_model(c)) return RMRT_OK;   // asked again: source fields may be detached later
   c->two_step = -1;
   const int q = lattice_q(c->p.lattice), es = (int)elem_size(c->p.storage);
@@ -975,15 +1099,8 @@ int two_step_prepare(rmrt_ctx* c, hipStream_t s) {
   }
   const size_t bytes = (size_t)q * c->hdom.ld * (size_t)es;
   if (c->p.pattern == RMRT_AA) {
-    // an in-place domain gets a second buffer, as long as that leaves most of
-    // the card's free memory to the caller
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > free_b / 8) return RMRT_OK;
-    if (hipMalloc(&c->second, bytes) != hipSuccess) {
-      (void)hipGetLastError();
-      c->second = nullptr;
-      return RMRT_OK;
-    }
+    c->second = second_buffer(bytes);
+    if (!c->second) return RMRT_OK;
     c->hdom.fb = c->second;
     HIP_TRY(hipMemcpyAsync(c->ddoms + c->dom, &c->hdom, sizeof(DomainDev), hipMemcpyHostToDevice, s));
   }
@@ -1008,7 +1125,27 @@ int launch_steps(rmrt_ctx* c, int n, long long first, hipStream_t s) {
   const bool ab = c->p.pattern == RMRT_AB;
   const int lead = (!ab && (first & 1)) ? 1 : 0;
   const bool two = c->two_step == 1 && !c->launch_set && two_step_model(c);
+  const int even = (n - lead) & ~1;   // steps of the tile passes
+  const bool tile = c->two_step == 2 && !c->launch_set && even >= 4 && tile_model(c, step_eq(c), step_force(c));
   for (int i = 0; i < n;) {
+    if (tile && i == lead) {
+      StepLaunch a;
+      std::memset(&a, 0, sizeof(a));
+      a.two_step = 2;
+      a.doms = c->ddoms + c->dom;
+      a.tile_items = c->tile_items;
+      a.grid = c->nitems;
+      a.sweep_w = c->sweep_w;
+      a.block = c->tile_threads;
+      a.eq = step_eq(c);
+      a.force = step_force(c);
+      a.bc = c->step_bc;
+      a.stream = s;
+      int rc = launch_tile_passes(a, c->p.lattice, c->p.storage, ab, even, first + i);
+      if (rc != RMRT_OK) return rc;
+      i += even;
+      continue;
+    }
     if (two && i >= lead && n - i >= 4) {
       StepLaunch a = two_step_launch(c);
       a.stream = s;
@@ -1373,6 +1510,7 @@ int rmrt_moments(rmrt_ctx* c, void* rho_out, void* u_out, int out_dtype, void* s
   a.out0 = rho_out;
   a.out1 = u_out;
   a.flag = out_dtype == RMRT_OUT_F32;
+  a.grid = (c->hdom.N + kAuxBlock - 1) / kAuxBlock;   // one node per thread, as for the local outputs
   hipError_t e = dispatch_moments(c->p.lattice, c->p.storage, a);
   if (e != hipSuccess) return fail(RMRT_EHIP, "moments launch: %s", hipGetErrorString(e));
   return RMRT_OK;
@@ -1887,6 +2025,20 @@ struct rmrt_batch {
   // default), or never (mode 0)
   int xcd_chunks = 1;
   std::vector<uint8_t> group_chunked;
+  // residuals of all domains in one launch (below, res_*): the parts (one per workgroup), the
+  // domains' states (device copy and what it holds), the parts' partial sums
+  // several steps per pass (rD2Q9): the tiles of all domains and the second
+  // buffers of in-place ones; 0 not asked for yet, 1 there, -1 not served
+  bool shape_set = false;      // the launch shape was set by hand: single steps of that shape only
+  int tile_steps = 0;
+  TileItem* tile_items = nullptr;
+  uint32_t ntile_items = 0, tile_w = 0, tile_threads = 0;
+  void* second = nullptr;
+  Tile* res_blocks = nullptr;
+  uint32_t nres_blocks = 0;
+  ResidualState* res_states = nullptr;
+  std::vector<ResidualState> res_host;
+  double* res_partials = nullptr;
   double* dres_all = nullptr;  // 2 * nd residual sums (device)
   double* hres_all = nullptr;  // pinned host copy
 };
@@ -2008,17 +2160,94 @@ void batch_advance(rmrt_batch* b, int n) {
   for (auto* c : b->ctxs) c->steps = b->steps;
 }
 
+// The tile path of a batch of rD2Q9 domains, set up on its first call of four
+// steps or more.
+int batch_tile_prepare(rmrt_batch* b, hipStream_t s) {
+  if (b->tile_steps != 0) return RMRT_OK;
+  b->tile_steps = -1;
+  size_t bytes = 0;
+  for (const rmrt_ctx* c : b->ctxs) {
+    if (!tile_model(c, b->equation, b->force)) return RMRT_OK;
+    bytes += ((size_t)9 * c->hdom.ld * elem_size(c->p.storage) + 255u) & ~(size_t)255u;
+  }
+  std::vector<TileItem> items;
+  std::vector<DomainDev> host;
+  try {
+    items = plan_tiles(b->ctxs, (uint32_t)b->cus, &b->tile_w, &b->tile_threads);
+    host.resize(b->ctxs.size());
+  } catch (const std::bad_alloc&) {
+    return RMRT_OK;
+  }
+  if (items.empty()) return RMRT_OK;
+  if (b->pattern == RMRT_AA) {
+    b->second = second_buffer(bytes);
+    if (!b->second) return RMRT_OK;
+    char* at = (char*)b->second;
+    for (size_t d = 0; d < b->ctxs.size(); ++d) {
+      rmrt_ctx* c = b->ctxs[d];
+      c->hdom.fb = at;
+      at += ((size_t)9 * c->hdom.ld * elem_size(c->p.storage) + 255u) & ~(size_t)255u;
+      host[d] = c->hdom;
+    }
+    HIP_TRY(hipMemcpyAsync(b->ddoms, host.data(), sizeof(DomainDev) * host.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));
+  }
+  if (hipMalloc(&b->tile_items, sizeof(TileItem) * items.size()) != hipSuccess) {
+    (void)hipGetLastError();
+    b->tile_items = nullptr;
+    return RMRT_OK;
+  }
+  HIP_TRY(hipMemcpyAsync(b->tile_items, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice, s));
+  HIP_TRY(hipStreamSynchronize(s));
+  b->ntile_items = (uint32_t)items.size();
+  b->tile_steps = 1;
+  return RMRT_OK;
+}
+
+// Launch n steps of every group from step `first`; rD2Q9 batches as tile
+// passes where they are set up.
+int batch_launch_steps(rmrt_batch* b, int n, long long first, hipStream_t s) {
+  const bool ab = b->pattern == RMRT_AB;
+  const int lead = (!ab && (first & 1)) ? 1 : 0, even = (n - lead) & ~1;
+  const bool tile = b->tile_steps == 1 && !b->shape_set && even >= 4;
+  auto single = [&](int from, int to) {
+    for (size_t gi = 0; gi < b->groups.size(); ++gi)
+      for (int i = from; i < to; ++i) {
+        int rc = batch_launch(b, first + i, s, gi);
+        if (rc != RMRT_OK) return rc;
+      }
+    return (int)RMRT_OK;
+  };
+  if (!tile) return single(0, n);
+  int rc = single(0, lead);
+  if (rc != RMRT_OK) return rc;
+  StepLaunch a;
+  std::memset(&a, 0, sizeof(a));
+  a.two_step = 2;
+  a.doms = b->ddoms;
+  a.tile_items = b->tile_items;
+  a.grid = b->ntile_items;
+  a.sweep_w = b->tile_w;
+  a.block = b->tile_threads;
+  a.eq = b->equation;
+  a.force = b->force;
+  a.bc = b->bc;
+  a.stream = s;
+  rc = launch_tile_passes(a, b->lattice, b->storage, ab, even, first + lead);
+  return rc == RMRT_OK ? single(lead + even, n) : rc;
+}
+
 // The graph of n steps of every group from step `first`, cached by (n,
-// parity, tile configuration); uploaded to stream `upload` when given.
-int batch_graph_for(rmrt_batch* b, int n, long long first, hipGraphExec_t* out, hipStream_t upload) {
+// parity, tile configuration); uploaded to the stream when asked for.
+int batch_graph_for(rmrt_batch* b, int n, long long first, hipGraphExec_t* out, hipStream_t stream, bool upload) {
   const auto key = std::make_tuple(n, (int)(first & 1), b->cfg);
   auto it = b->graphs.find(key);
   if (it == b->graphs.end()) {
+    int rc = n >= 4 ? batch_tile_prepare(b, stream) : RMRT_OK;
+    if (rc != RMRT_OK) return rc;
     if (!b->cap) HIP_TRY(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
-    int rc = RMRT_OK;
-    for (size_t gi = 0; gi < b->groups.size() && rc == RMRT_OK; ++gi)
-      for (int i = 0; i < n && rc == RMRT_OK; ++i) rc = batch_launch(b, first + i, b->cap, gi);
+    rc = batch_launch_steps(b, n, first, b->cap);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(b->cap, &g);
     if (rc != RMRT_OK) {
@@ -2032,7 +2261,7 @@ int batch_graph_for(rmrt_batch* b, int n, long long first, hipGraphExec_t* out, 
     if (e != hipSuccess) return fail(RMRT_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
     if (b->graphs.size() >= 16) drop_graphs(b->graphs);
     it = b->graphs.emplace(key, ge).first;
-    if (upload) HIP_TRY(hipGraphUpload(ge, upload));
+    if (upload) HIP_TRY(hipGraphUpload(ge, stream));
   }
   *out = it->second;
   return RMRT_OK;
@@ -2040,7 +2269,7 @@ int batch_graph_for(rmrt_batch* b, int n, long long first, hipGraphExec_t* out, 
 
 int batch_graph(rmrt_batch* b, int n, hipStream_t s) {
   hipGraphExec_t ge = nullptr;
-  int rc = batch_graph_for(b, n, b->steps, &ge, nullptr);
+  int rc = batch_graph_for(b, n, b->steps, &ge, s, false);
   if (rc != RMRT_OK) return rc;
   HIP_TRY(hipGraphLaunch(ge, s));
   batch_advance(b, n);
@@ -2065,6 +2294,51 @@ int batch_step_impl(rmrt_batch* b, int nsteps, hipStream_t s) {
   return RMRT_OK;
 }
 
+// Buffers and tables of rmrt_batch_residual: set up on its first call; the
+// states are sent again whenever a domain's previous velocity was set or reset.
+int batch_residual_setup(rmrt_batch* b, hipStream_t s) {
+  const size_t nd = (size_t)b->nd;
+  if (!b->dres_all) HIP_TRY(hipMalloc(&b->dres_all, sizeof(double) * 2 * nd));
+  if (!b->hres_all) HIP_TRY(hipHostMalloc(&b->hres_all, sizeof(double) * 2 * nd, hipHostMallocDefault));
+  for (rmrt_ctx* c : b->ctxs) {
+    const int K = c->p.equation == RMRT_NSE ? c->v.d : 1;
+    if (!c->uprev) HIP_TRY(hipMalloc(&c->uprev, sizeof(double) * (size_t)K * c->hdom.N));
+  }
+  if (!b->res_blocks) {
+    std::vector<Tile> blocks;
+    for (size_t d = 0; d < nd; ++d) {
+      const unsigned g = aux_grid(b->ctxs[d]->hdom.N);
+      for (unsigned k = 0; k < g; ++k) blocks.push_back(Tile{(uint32_t)d, k, g, 0});
+    }
+    if (!b->res_partials) HIP_TRY(hipMalloc(&b->res_partials, sizeof(double) * 2 * blocks.size()));
+    if (!b->res_states) HIP_TRY(hipMalloc(&b->res_states, sizeof(ResidualState) * nd));
+    Tile* dev = nullptr;
+    HIP_TRY(hipMalloc(&dev, sizeof(Tile) * blocks.size()));
+    b->res_blocks = dev;
+    b->nres_blocks = (uint32_t)blocks.size();
+    b->res_host.clear();
+    HIP_TRY(hipMemcpyAsync(dev, blocks.data(), sizeof(Tile) * blocks.size(), hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));   // the copy reads a host local
+  }
+  std::vector<ResidualState> want(nd);
+  uint32_t first = 0;
+  bool same = b->res_host.size() == nd;
+  for (size_t d = 0; d < nd; ++d) {
+    const rmrt_ctx* c = b->ctxs[d];
+    const uint32_t g = aux_grid(c->hdom.N);
+    want[d] = ResidualState{c->uprev, c->have_prev ? 1u : 0u, first, g, 0u};
+    same = same && b->res_host[d].have_prev == want[d].have_prev && b->res_host[d].prev == want[d].prev;
+    first += g;
+  }
+  if (!same) {
+    b->res_host.clear();   // (not the device's content until the copy has ended)
+    HIP_TRY(hipMemcpyAsync(b->res_states, want.data(), sizeof(ResidualState) * nd, hipMemcpyHostToDevice, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    b->res_host = want;
+  }
+  return RMRT_OK;
+}
+
 void batch_release(rmrt_batch* b) {
   (void)hipDeviceSynchronize();  // work issued on any stream may still use the buffers
   drop_graphs(b->graphs);
@@ -2078,6 +2352,11 @@ void batch_release(rmrt_batch* b) {
   b->ctxs.clear();
   if (b->dtiles) (void)hipFree(b->dtiles);
   if (b->ddoms) (void)hipFree(b->ddoms);
+  if (b->tile_items) (void)hipFree(b->tile_items);
+  if (b->second) (void)hipFree(b->second);
+  if (b->res_blocks) (void)hipFree(b->res_blocks);
+  if (b->res_states) (void)hipFree(b->res_states);
+  if (b->res_partials) (void)hipFree(b->res_partials);
   if (b->dres_all) (void)hipFree(b->dres_all);
   if (b->hres_all) (void)hipHostFree(b->hres_all);
 }
@@ -2188,6 +2467,7 @@ int rmrt_batch_domain(rmrt_batch* b, int d, rmrt_ctx** out) {
 int rmrt_batch_set_config(rmrt_batch* b, int cfg) {
   if (!b) return fail(RMRT_EINVAL, "batch is NULL");
   if (cfg < 0 || cfg >= kNumTileShapes) return fail(RMRT_EINVAL, "config %d out of range", cfg);
+  b->shape_set = true;
   return batch_build_tiles(b, cfg, nullptr);
 }
 
@@ -2205,12 +2485,12 @@ int rmrt_batch_step_prepare(rmrt_batch* b, int nsteps, void* stream) {
   long long first = b->steps;
   int left = nsteps;
   while (left >= kGraphChunk) {
-    int rc = batch_graph_for(b, kGraphChunk, first, &ge, s);
+    int rc = batch_graph_for(b, kGraphChunk, first, &ge, s, true);
     if (rc != RMRT_OK) return rc;
     first += kGraphChunk;
     left -= kGraphChunk;
   }
-  if (left > 1) return batch_graph_for(b, left, first, &ge, s);
+  if (left > 1) return batch_graph_for(b, left, first, &ge, s, true);
   return RMRT_OK;
 }
 
@@ -2222,6 +2502,7 @@ int rmrt_batch_autotune(rmrt_batch* b, int steps, void* stream, int* chosen) {
   HIP_TRY(hipEventCreate(&ev.e0));
   HIP_TRY(hipEventCreate(&ev.e1));
   hipEvent_t e0 = ev.e0, e1 = ev.e1;
+  b->shape_set = true;   // the shapes of single steps are timed
   int best = -1;
   float best_ms = 1e30f;
   for (int cfg = 0; cfg < kNumTileShapes; ++cfg) {
@@ -2288,8 +2569,9 @@ int rmrt_batch_autotune(rmrt_batch* b, int steps, void* stream, int* chosen) {
       HIP_TRY(hipEventElapsedTime(&mode_ms[mode], e0, e1));
     }
     b->xcd_chunks = mode_ms[1] <= mode_ms[0] ? 1 : 0;
-    drop_graphs(b->graphs);
   }
+  b->shape_set = false;   // tile passes, where the batch has them, stay the faster form
+  drop_graphs(b->graphs);
   if (chosen) *chosen = best;
   return RMRT_OK;
 }
@@ -2298,6 +2580,7 @@ int rmrt_batch_set_xcd_chunks(rmrt_batch* b, int mode) {
   if (!b) return fail(RMRT_EINVAL, "batch is NULL");
   if (mode != 0 && mode != 1) return fail(RMRT_EINVAL, "xcd chunk mode must be 0 or 1");
   b->xcd_chunks = mode;
+  b->shape_set = true;
   drop_graphs(b->graphs);
   return RMRT_OK;
 }
@@ -2316,6 +2599,7 @@ int rmrt_batch_get_xcd_chunks(const rmrt_batch* b, int* mode, int* chunked_group
 int rmrt_batch_set_group_bytes(rmrt_batch* b, size_t bytes) {
   if (!b) return fail(RMRT_EINVAL, "batch is NULL");
   b->group_bytes = bytes;
+  b->shape_set = true;
   batch_make_groups(b);
   return RMRT_OK;
 }
@@ -2330,21 +2614,27 @@ int rmrt_batch_get_group_bytes(const rmrt_batch* b, size_t* bytes, int* ngroups)
 int rmrt_batch_residual(rmrt_batch* b, double* r, void* stream) {
   if (!b || !r) return fail(RMRT_EINVAL, "batch or r is NULL");
   hipStream_t s = (hipStream_t)stream;
-  if (!b->dres_all) HIP_TRY(hipMalloc(&b->dres_all, sizeof(double) * 2 * b->nd));
-  if (!b->hres_all) HIP_TRY(hipHostMalloc(&b->hres_all, sizeof(double) * 2 * b->nd, hipHostMallocDefault));
-  for (int d = 0; d < b->nd; ++d) {
-    rmrt_ctx* c = b->ctxs[d];
-    const int K = c->p.equation == RMRT_NSE ? c->v.d : 1;
-    if (!c->uprev) HIP_TRY(hipMalloc(&c->uprev, sizeof(double) * (size_t)K * c->hdom.N));
-    AuxLaunch a = aux_of(c, s);
-    a.out0 = c->partials;
-    a.out1 = c->uprev;
-    a.flag = c->have_prev ? 1 : 0;
-    hipError_t e = dispatch_residual(c->p.lattice, c->p.storage, a);
-    if (e != hipSuccess) return fail(RMRT_EHIP, "residual launch: %s", hipGetErrorString(e));
-    e = launch_reduce_final(c->partials, a.grid, b->dres_all + 2 * d, 2, s);
-    if (e != hipSuccess) return fail(RMRT_EHIP, "residual final: %s", hipGetErrorString(e));
+  int rc0;
+  try {
+    rc0 = batch_residual_setup(b, s);
+  } catch (const std::bad_alloc&) {
+    return fail(RMRT_ENOMEM, "out of host memory");
   }
+  if (rc0 != RMRT_OK) return rc0;
+  // every domain in one launch; the domains share lattice, storage, pattern,
+  // equation and step count, and the walled form of the kernel covers all
+  AuxLaunch a = aux_of(b->ctxs[0], s);
+  a.doms = b->ddoms;
+  a.bc = 0;
+  for (const rmrt_ctx* c : b->ctxs) a.bc |= (c->hdom.walls != 0 || c->hdom.has_solid) ? 1 : 0;
+  a.blocks = b->res_blocks;
+  a.grid = b->nres_blocks;
+  a.states = b->res_states;
+  a.nstates = (unsigned)b->nd;
+  a.out0 = b->res_partials;
+  a.out1 = b->dres_all;
+  hipError_t e = dispatch_residual(b->lattice, b->storage, a);
+  if (e != hipSuccess) return fail(RMRT_EHIP, "residual launch: %s", hipGetErrorString(e));
   HIP_TRY(hipMemcpyAsync(b->hres_all, b->dres_all, sizeof(double) * 2 * b->nd, hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   int rc = RMRT_OK;

@@ -1,6 +1,6 @@
-// How a domain is split into the work items of the two-step kernel
-// (lbm_two_step.hpp), and whether that kernel is the faster one for it.  Host
-// code without GPU calls.
+// How domains are split into the work items of the two-step kernel
+// (lbm_two_step.hpp) and of the tile kernel (lbm_tile_steps.hpp), and whether
+// those kernels are the faster ones for them.  Host code without GPU calls.
 #pragma once
 
 #include <stdint.h>
@@ -97,6 +97,50 @@ inline std::vector<SweepItem> sweep_items(const SweepPlan& p, uint32_t nx, uint3
     out[b] = list[first + b / 8];
   }
   return out;
+}
+
+// ---------------------------------------------------------------------------
+// Tiles of several steps (rD2Q9)
+// ---------------------------------------------------------------------------
+struct TileSplit {
+  uint32_t cx = 0, cy = 0, w = 0;   // inner nodes of a tile, width with the ring
+  uint64_t tiles = ~0ull;
+};
+
+// The split of an nx x ny domain into the fewest tiles of at most `nodes`
+// nodes, ring included (a tile over the whole of x has none there).
+inline TileSplit split_tiles(uint32_t nx, uint32_t ny, uint32_t nodes, uint32_t ring) {
+  TileSplit best;
+  for (uint32_t ntx = 1; ntx <= nx; ++ntx) {
+    const uint32_t cx = (nx + ntx - 1) / ntx;
+    if ((uint64_t)(ntx - 1) * cx >= nx) continue;
+    const uint32_t w = ntx == 1 ? nx : cx + 2 * ring;
+    if (ntx > 1 && cx < 8) break;
+    const uint32_t rows = nodes / w;
+    if (rows < 2 * ring + 1) continue;
+    const uint32_t cymax = std::min(ny, rows - 2 * ring), nty = (ny + cymax - 1) / cymax;
+    const uint64_t tiles = (uint64_t)ntx * nty;
+    if (tiles < best.tiles) best = TileSplit{cx, (ny + nty - 1) / nty, w, tiles};
+  }
+  return best;
+}
+
+// Time of a pass of `tiles` tiles of up to `blocks` nodes per thread and `steps`
+// steps with `slots` workgroups at once (us): a launch, and per round the first
+// loads, then each thread's nodes.  rD2Q9 FP32 with 512 threads, FP64 with 256
+// or 512; estimated / measured: FP32 2048 x 1024 58.5 / 57, 256 x 256 6.9 / 8.2,
+// FP64 2048 x 1024 (512 threads) 128 / 121, 64 x 32 (256 threads) 7.0 / 6.5.
+inline double tile_pass_us(uint64_t tiles, uint32_t blocks, uint32_t slots, int es, uint32_t threads, uint32_t steps) {
+  const double rounds = (double)((tiles + slots - 1) / slots);
+  const double load = es == 8 && threads <= 256 ? 0.8 : 0.9, step = es == 4 ? 0.75 : threads <= 256 ? 0.8 : 1.0;
+  return 1.5 + rounds * (1.5 + blocks * (load + steps * step));
+}
+// Is a pass faster than the single steps it stands for?  Those take a replayed
+// launch and their bytes at the rate of the memory-side cache (FP32 64 x 32 2.7
+// us, 512 x 512 4.5, 2048 x 1024 21; FP64 2048 x 1024 42).
+inline bool tiles_pay(double pass_us, uint64_t nodes, int es, uint32_t steps) {
+  const double single = 2.5 + (double)nodes * 18.0 * es / 8.4e6;
+  return pass_us < 0.9 * steps * single;
 }
 
 }  // namespace rmrt

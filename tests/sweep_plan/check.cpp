@@ -31,6 +31,24 @@ static int check(uint32_t nx, uint32_t ny, uint32_t nz, int q, int es, uint32_t 
   return 0;
 }
 
+static int check_tiles(uint32_t nx, uint32_t ny, uint32_t nodes, uint32_t ring) {
+  const TileSplit t = split_tiles(nx, ny, nodes, ring);
+  if (t.cx == 0) return 0;   // no tile fits: single steps
+  uint64_t n = 0;
+  std::vector<unsigned char> seen((size_t)nx * ny, 0);
+  for (uint32_t y = 0; y < ny; y += t.cy)
+    for (uint32_t x = 0; x < nx; x += t.cx) {
+      const uint32_t cx = std::min(t.cx, nx - x), cy = std::min(t.cy, ny - y), w = cx == nx ? nx : cx + 2 * ring;
+      if (w > t.w || (uint64_t)w * (cy + 2 * ring) > nodes) return fprintf(stderr, "bad tile in %u x %u\n", nx, ny), 1;
+      for (uint32_t j = y; j < y + cy; ++j)
+        for (uint32_t i = x; i < x + cx; ++i) seen[i + (size_t)nx * j] += 1;
+      ++n;
+    }
+  for (unsigned char s : seen)
+    if (s != 1) return fprintf(stderr, "a node of %u x %u in %d tiles\n", nx, ny, s), 1;
+  return n > t.tiles;
+}
+
 int main() {
   const uint32_t sizes[] = {4, 5, 7, 16, 31, 32, 33, 64, 65, 100, 127, 223, 256, 257, 512, 513, 700, 1300};
   const struct { int q, es; uint32_t columns; } kinds[] = {{19, 4, 1536}, {19, 8, 1024}, {27, 4, 1024}};
@@ -44,6 +62,13 @@ int main() {
           bad += check(nx, ny, nz, k.q, k.es, k.columns, 7);
           n += 2;
         }
+  const uint32_t flat[] = {8, 9, 13, 64, 77, 128, 255, 256, 257, 512, 777, 1024, 2048, 5000};
+  for (uint32_t nodes = 256; nodes <= 2048; nodes += 256)
+    for (uint32_t nx : flat)
+      for (uint32_t ny : flat) {
+        bad += check_tiles(nx, ny, nodes, 4);
+        ++n;
+      }
   if (bad) return 1;
   printf("ok %d\n", n);
   return 0;
