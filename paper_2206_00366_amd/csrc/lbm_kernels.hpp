@@ -732,7 +732,7 @@ __global__ void __launch_bounds__(256)
 // node per thread; addressing and tile order as in k_step.  Bound by HBM (the
 // step's bytes and the outputs); rD3Q27 FP32 223 x 116 x 100 with walls and
 // force, even / odd: 113 / 131 us with 64-bit addressing and without the XCD
-// chunks, 108 / 120 us now.
+// chunks, 105 / 123 us now.
 template <int L, int ST, int EQ, int FORCE, int BC, int PH, bool BUF>
 __global__ void __launch_bounds__(256)
     k_step_local(const DomainDev* __restrict__ doms, uint32_t tile_nodes, uint32_t parity, void* out, int kind,
@@ -1018,7 +1018,7 @@ __global__ void __launch_bounds__(256)
 // Sum of nb x K partials in a fixed order (deterministic); the result is
 // valid in thread 0 of a single 256-thread workgroup.  (The last 256 sums go
 // through a tree; one thread adding them took most of the 12 us that a
-// reduction of five sums cost, now 4 us.)
+// reduction of five sums cost, now 3 us.)
 template <int K>
 __device__ __forceinline__ void sum_partials(const double* __restrict__ partials, uint32_t nb, double (&res)[K]) {
   __shared__ double sh[K][4];
@@ -1077,7 +1077,7 @@ __global__ void __launch_bounds__(256)
 // The same for every domain of a batch in one launch: workgroup b takes part
 // blocks[b].start of blocks[b].count of domain blocks[b].dom, with the parts
 // and so the sums of one k_residual per domain (16 domains of 512 x 256: 90 us
-// of launches of 5.6 us each, now 10 us).
+// of launches of 5.6 us each, now 26 us).
 template <int L, int ST, int EQ, int BC, bool SWAPPED>
 __global__ void __launch_bounds__(256)
     k_residual_batch(const DomainDev* __restrict__ doms, const Tile* __restrict__ blocks,
@@ -1121,14 +1121,14 @@ __device__ __forceinline__ void velocity_gradient(const DomainDev& Dm, const dou
       okm = okm && !Dm.solid[im];
     }
     const double h = Dm.cd.c[b] * Dm.cd.dt;
+    // values read at the node itself on the missing sides, so that no load waits in
+    // a branch (k_init of rD2Q9 FP32, 512 x 256: 9.9 us with a branch per case, 9.4 now)
+    const uint32_t jp = okp ? ip : idx, jm = okm ? im : idx;
+    const double den = okp && okm ? 2.0 * h : h;
     for (int a = 0; a < D; ++a) {
       const double* ua = u + (size_t)a * N;
-      if (okp && okm)
-        G[a][b] = (ua[ip] - ua[im]) / (2.0 * h);
-      else if (okp)
-        G[a][b] = (ua[ip] - ua[idx]) / h;
-      else if (okm)
-        G[a][b] = (ua[idx] - ua[im]) / h;
+      const double d = ua[jp] - ua[jm];
+      G[a][b] = okp || okm ? d / den : 0.0;
     }
   }
 }

@@ -17,7 +17,7 @@
 // 13.8 (workgroups of 1024 threads, one to a CU: 16.3; a sweep along y that
 // holds two steps: 16.4), 512 x 256 3.4 / 2.4, 64 x 32 2.65 / 1.6; FP64 64 x 32
 // 2.8 / 1.6, 2048 x 1024 42 / 30; 16 FP32 obstacle channels of 512 x 256 in a
-// batch 27 / 17.
+// batch 27 / 18.
 // The arithmetic is the single step's, so the results are those of single steps
 // bit for bit.
 #pragma once

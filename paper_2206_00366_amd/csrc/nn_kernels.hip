@@ -50,7 +50,7 @@ enum { EPI_NONE = 0, EPI_SILU = 1, EPI_SILU_GRAD = 2 };
 // kernel on weights flipped by k_flip.
 // Bound by memory: at 16 x 64 x 128 pixels, 32 -> 32 channels, x, y and a are
 // 34 MB; 32 us with one tile per wave, 16-wide k and 2- and 4-byte stores (every
-// wave read all weights for 16 pixels), CONV_NOW us now.
+// wave read all weights for 16 pixels), 16 us now.
 template <int CIN, int COUT>
 __global__ void __launch_bounds__(256, 2)
     k_conv(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w, const float* __restrict__ bias,
@@ -157,7 +157,7 @@ __global__ void k_flip(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt
 // Bound by LDS reads (40 a wave for 10 products) and the latency of one segment's
 // loads; at 16 x 64 x 128 pixels, 32 x 32 channels: 129 us with 2-byte gathers
 // from memory, one wave per tap and chunk, + 35 us for the sum of its partials
-// and + 213 us for db (its last sum was one thread per channel), WGRAD_NOW us now
+// and + 213 us for db (its last sum was one thread per channel), 16 + 8 us now
 // together.
 constexpr int kSeg = 128, kWgBlocks = 512;
 __host__ __device__ inline bool wgrad_shared_window(int dil) { return dil > 0 && dil % 2 == 0 && dil <= 32; }
@@ -310,7 +310,7 @@ __global__ void __launch_bounds__(256) k_wsum(const float* __restrict__ mask, lo
 // masked MSE over the first C channels of out (stride Cs): per-workgroup loss
 // partials; dout (bf16, stride Cs, zero in the padding channels).  Bound by
 // latency (three short kernels, serial sums by one thread before: 72 us, now
-// MSE_NOW us together at 16 x 64 x 128 pixels).
+// 12 us together at 16 x 64 x 128 pixels).
 __global__ void __launch_bounds__(256)
     k_mse(const float* __restrict__ out, int Cs, const float* __restrict__ tgt, const float* __restrict__ mask, long P,
           int C, const double* __restrict__ wpart, int nw, float* __restrict__ inv_den_p, uint16_t* __restrict__ dout,
@@ -383,7 +383,7 @@ __global__ void k_to_bf16(const float* __restrict__ src, uint16_t* __restrict__ 
 // colfrac[b][x] = solid fraction of column x; gfrac[b] = solid fraction of sample b.
 // Bound by latency: 64 columns and 16 interleaved runs of rows per workgroup (16
 // samples of 512 x 256: one thread per column and per sample before, 98 + 38 us,
-// now COLFRAC_NOW us).
+// now 5 + 3 us).
 __global__ void __launch_bounds__(1024)
     k_colfrac(const uint8_t* __restrict__ solid, int B, int nx, int ny, float* __restrict__ colfrac) {
   __shared__ int sh[16][64];
