@@ -157,7 +157,7 @@ __global__ void k_flip(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt
 // Bound by LDS reads (40 a wave for 10 products) and the latency of one segment's
 // loads; at 16 x 64 x 128 pixels, 32 x 32 channels: 129 us with 2-byte gathers
 // from memory, one wave per tap and chunk, + 35 us for the sum of its partials
-// and + 213 us for db (its last sum was one thread per channel), 16 + 8 us now
+// and + 213 us for db (its last sum was one thread per channel), 16 + 5 us now
 // together.
 constexpr int kSeg = 128, kWgBlocks = 512;
 __host__ __device__ inline bool wgrad_shared_window(int dil) { return dil > 0 && dil % 2 == 0 && dil <= 32; }
@@ -262,26 +262,29 @@ __global__ void __launch_bounds__(256, 2)
 }
 
 // Sums of n partials of `len` floats (out) and `lenb` floats (outb, may be
-// null): 16 neighbouring outputs and 16 interleaved runs of partials per
-// workgroup, then a tree over the runs: a fixed order.
-__global__ void __launch_bounds__(256)
+// null): 32 neighbouring outputs (a whole line of each partial) and 32
+// interleaved runs of partials per workgroup, then a tree over the runs: a fixed
+// order.  Bound by latency and the read of the partials (19 MB for 32 x 32
+// channels: 7.9 us with 16 outputs and 16 runs per workgroup, 4.8 now).
+constexpr int kSumOuts = 32, kSumRuns = 32;
+__global__ void __launch_bounds__(kSumOuts* kSumRuns)
     k_sum_partials(const float* __restrict__ part, float* __restrict__ out, int len, const float* __restrict__ partb,
                    float* __restrict__ outb, int lenb, int n) {
-  __shared__ float sh[16][17];
-  const int e = threadIdx.x & 15, r = threadIdx.x >> 4;
-  const int nb = (len + 15) / 16;
+  __shared__ float sh[kSumRuns][kSumOuts + 1];
+  const int e = threadIdx.x % kSumOuts, r = threadIdx.x / kSumOuts;
+  const int nb = (len + kSumOuts - 1) / kSumOuts;
   const bool second = (int)blockIdx.x >= nb;
   const float* src = second ? partb : part;
   float* dst = second ? outb : out;
   const int l = second ? lenb : len;
-  const int o = ((int)blockIdx.x - (second ? nb : 0)) * 16 + e;
+  const int o = ((int)blockIdx.x - (second ? nb : 0)) * kSumOuts + e;
   float s = 0.f;
   if (o < l)
 #pragma unroll 8
-    for (int k = r; k < n; k += 16) s += src[(long)k * l + o];
+    for (int k = r; k < n; k += kSumRuns) s += src[(long)k * l + o];
   sh[r][e] = s;
   __syncthreads();
-  for (int d = 8; d > 0; d >>= 1) {
+  for (int d = kSumRuns / 2; d > 0; d >>= 1) {
     if (r < d) sh[r][e] += sh[r + d][e];
     __syncthreads();
   }
@@ -567,8 +570,9 @@ hipError_t launch_wgrad(const uint16_t* x, const uint16_t* dy, int B, int H, int
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int lenb = db ? Cout : 0;
-  hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)((len + 15) / 16 + (lenb + 15) / 16)), dim3(256), 0, s, part, dw, len,
-                     partb, db, lenb, slots);
+  const int groups = (len + kSumOuts - 1) / kSumOuts + (lenb + kSumOuts - 1) / kSumOuts;
+  hipLaunchKernelGGL(k_sum_partials, dim3((unsigned)groups), dim3(kSumOuts * kSumRuns), 0, s, part, dw, len, partb, db,
+                     lenb, slots);
   return hipGetLastError();
 }
 
