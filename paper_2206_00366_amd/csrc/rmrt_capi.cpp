@@ -767,6 +767,7 @@ struct rmrt_ctx {
   SweepItem* items = nullptr;
   TileItem* tile_items = nullptr;   // rD2Q9: several steps per pass (k_tile_steps) instead
   uint32_t nitems = 0, sweep_w = 0, tile_threads = 0;
+  TileRule tile_rule;
 };
 
 namespace {
@@ -953,17 +954,29 @@ bool tile_model(const rmrt_ctx* c, int eq, int force) {
   return c->p.n[0] >= 8 && c->p.n[1] >= 8;
 }
 
+static_assert(kTileRing == 4, "tile_call pairs passes of up to four steps");
+TileKind tile_kind(int storage, int bc, int force, size_t domains) {
+  TileKind k;
+  k.es = (int)elem_size(storage);
+  k.bounded = bc != 0;
+  k.links = bc == 2;
+  k.sourced = force != F_NONE;
+  k.batch = domains > 1;
+  return k;
+}
+
 // Tiles of the given domains, or none where single steps are faster: of the
 // workgroups and of the tile sizes of 1 .. 4 nodes per thread the ones with the
-// shortest pass.
-std::vector<TileItem> plan_tiles(const std::vector<rmrt_ctx*>& doms, uint32_t cus, uint32_t* width, uint32_t* threads) {
-  const int es = (int)elem_size(doms[0]->p.storage);
+// shortest pass; and the pass lengths that pay.
+std::vector<TileItem> plan_tiles(const std::vector<rmrt_ctx*>& doms, int bc, int force, uint32_t cus, uint32_t* width,
+                                 uint32_t* threads, TileRule* rule) {
+  const TileKind kind = tile_kind(doms[0]->p.storage, bc, force, doms.size());
   double best_us = 1e300;
   uint32_t best = 0;
   uint64_t nodes = 0;
   for (const rmrt_ctx* c : doms) nodes += c->hdom.N;
-  for (uint32_t twice = 0; twice < (es == 8 ? 2u : 1u); ++twice) {
-    const uint32_t nt = kTileThreads(doms[0]->p.storage) << twice, slots = cus * (2u - twice);
+  for (uint32_t twice = 0; twice < (kind.es == 8 ? 2u : 1u); ++twice) {
+    const uint32_t nt = kTileThreads(doms[0]->p.storage) << twice;
     for (uint32_t blocks = 1; blocks <= kTileNodes; ++blocks) {
       uint64_t tiles = 0;
       bool fits = true;
@@ -973,17 +986,18 @@ std::vector<TileItem> plan_tiles(const std::vector<rmrt_ctx*>& doms, uint32_t cu
         tiles += t.tiles;
       }
       if (!fits) continue;
-      const double us = tile_pass_us(tiles, blocks, slots, es, nt, kTileRing);
+      const double us = tile_pass_us(kind, tiles, blocks, cus, nt, kTileRing);
       if (us < best_us) {
         best_us = us;
         best = blocks * nt;
         *threads = nt;
+        for (uint32_t n = 2; n <= kTileRing; ++n) rule->pays[n] = tile_pass_pays(kind, tiles, blocks, cus, nt, nodes, n);
       }
     }
   }
   std::vector<TileItem> items;
   *width = 0;
-  if (best == 0 || !tiles_pay(best_us, nodes, es, kTileRing)) return items;
+  if (best == 0 || !rule->pays[kTileRing]) return items;
   for (size_t d = 0; d < doms.size(); ++d) {
     const uint32_t nx = doms[d]->hdom.nx, ny = doms[d]->hdom.ny;
     const TileSplit t = split_tiles(nx, ny, best, kTileRing);
@@ -1012,15 +1026,6 @@ void* second_buffer(size_t bytes) {
   return p;
 }
 
-// Steps of pass k of the passes that take m (even) steps between them: an even
-// number of passes of at most kTileRing steps, so that the state ends in the
-// buffer where single steps would leave it.
-int tile_passes(int m) { return 2 * ((m + 2 * (int)kTileRing - 1) / (2 * (int)kTileRing)); }
-int tile_pass_steps(int m, int k) {
-  const int passes = tile_passes(m);
-  return m / passes + (k < m % passes ? 1 : 0);
-}
-
 StepLaunch two_step_launch(const rmrt_ctx* c) {
   StepLaunch a;
   std::memset(&a, 0, sizeof(a));
@@ -1038,7 +1043,7 @@ int tile_prepare(rmrt_ctx* c, hipStream_t s) {
   c->two_step = -1;
   std::vector<TileItem> items;
   try {
-    items = plan_tiles({c}, (uint32_t)c->cus, &c->sweep_w, &c->tile_threads);
+    items = plan_tiles({c}, c->step_bc, step_force(c), (uint32_t)c->cus, &c->sweep_w, &c->tile_threads, &c->tile_rule);
   } catch (const std::bad_alloc&) {
     return RMRT_OK;
   }
@@ -1061,12 +1066,12 @@ int tile_prepare(rmrt_ctx* c, hipStream_t s) {
   return RMRT_OK;
 }
 
-// The passes of m (even) steps from step `first`.
-int launch_tile_passes(StepLaunch a, int lattice, int storage, bool ab, int m, long long first) {
+// The passes of a call from step `first`.
+int launch_tile_passes(StepLaunch a, int lattice, int storage, bool ab, const TileCall& call, long long first) {
   const uint32_t cur = ab ? (uint32_t)(first & 1) : 0u;
-  for (int k = 0; k < tile_passes(m); ++k) {
+  for (int k = 0; k < call.passes(); ++k) {
     a.parity = cur ^ (uint32_t)(k & 1);
-    a.pass_steps = (uint32_t)tile_pass_steps(m, k);
+    a.pass_steps = (uint32_t)call.pass_steps(k);
     hipError_t e = dispatch_step(lattice, storage, a);
     if (e != hipSuccess) return fail(RMRT_EHIP, "tile pass launch failed: %s", hipGetErrorString(e));
   }
@@ -1125,10 +1130,11 @@ int launch_steps(rmrt_ctx* c, int n, long long first, hipStream_t s) {
   const bool ab = c->p.pattern == RMRT_AB;
   const int lead = (!ab && (first & 1)) ? 1 : 0;
   const bool two = c->two_step == 1 && !c->launch_set && two_step_model(c);
-  const int even = (n - lead) & ~1;   // steps of the tile passes
-  const bool tile = c->two_step == 2 && !c->launch_set && even >= 4 && tile_model(c, step_eq(c), step_force(c));
+  TileCall call;
+  if (c->two_step == 2 && !c->launch_set && tile_model(c, step_eq(c), step_force(c)))
+    call = tile_call(c->tile_rule, (n - lead) & ~1);
   for (int i = 0; i < n;) {
-    if (tile && i == lead) {
+    if (call.passes() > 0 && i == lead) {
       StepLaunch a;
       std::memset(&a, 0, sizeof(a));
       a.two_step = 2;
@@ -1141,9 +1147,9 @@ int launch_steps(rmrt_ctx* c, int n, long long first, hipStream_t s) {
       a.force = step_force(c);
       a.bc = c->step_bc;
       a.stream = s;
-      int rc = launch_tile_passes(a, c->p.lattice, c->p.storage, ab, even, first + i);
+      int rc = launch_tile_passes(a, c->p.lattice, c->p.storage, ab, call, first + i);
       if (rc != RMRT_OK) return rc;
-      i += even;
+      i += call.steps();
       continue;
     }
     if (two && i >= lead && n - i >= 4) {
@@ -2033,6 +2039,7 @@ struct rmrt_batch {
   int tile_steps = 0;
   TileItem* tile_items = nullptr;
   uint32_t ntile_items = 0, tile_w = 0, tile_threads = 0;
+  TileRule tile_rule;
   void* second = nullptr;
   Tile* res_blocks = nullptr;
   uint32_t nres_blocks = 0;
@@ -2173,7 +2180,7 @@ int batch_tile_prepare(rmrt_batch* b, hipStream_t s) {
   std::vector<TileItem> items;
   std::vector<DomainDev> host;
   try {
-    items = plan_tiles(b->ctxs, (uint32_t)b->cus, &b->tile_w, &b->tile_threads);
+    items = plan_tiles(b->ctxs, b->bc, b->force, (uint32_t)b->cus, &b->tile_w, &b->tile_threads, &b->tile_rule);
     host.resize(b->ctxs.size());
   } catch (const std::bad_alloc&) {
     return RMRT_OK;
@@ -2208,8 +2215,9 @@ int batch_tile_prepare(rmrt_batch* b, hipStream_t s) {
 // passes where they are set up.
 int batch_launch_steps(rmrt_batch* b, int n, long long first, hipStream_t s) {
   const bool ab = b->pattern == RMRT_AB;
-  const int lead = (!ab && (first & 1)) ? 1 : 0, even = (n - lead) & ~1;
-  const bool tile = b->tile_steps == 1 && !b->shape_set && even >= 4;
+  const int lead = (!ab && (first & 1)) ? 1 : 0;
+  TileCall call;
+  if (b->tile_steps == 1 && !b->shape_set) call = tile_call(b->tile_rule, (n - lead) & ~1);
   auto single = [&](int from, int to) {
     for (size_t gi = 0; gi < b->groups.size(); ++gi)
       for (int i = from; i < to; ++i) {
@@ -2218,7 +2226,7 @@ int batch_launch_steps(rmrt_batch* b, int n, long long first, hipStream_t s) {
       }
     return (int)RMRT_OK;
   };
-  if (!tile) return single(0, n);
+  if (call.passes() == 0) return single(0, n);
   int rc = single(0, lead);
   if (rc != RMRT_OK) return rc;
   StepLaunch a;
@@ -2233,8 +2241,8 @@ int batch_launch_steps(rmrt_batch* b, int n, long long first, hipStream_t s) {
   a.force = b->force;
   a.bc = b->bc;
   a.stream = s;
-  rc = launch_tile_passes(a, b->lattice, b->storage, ab, even, first + lead);
-  return rc == RMRT_OK ? single(lead + even, n) : rc;
+  rc = launch_tile_passes(a, b->lattice, b->storage, ab, call, first + lead);
+  return rc == RMRT_OK ? single(lead + call.steps(), n) : rc;
 }
 
 // The graph of n steps of every group from step `first`, cached by (n,

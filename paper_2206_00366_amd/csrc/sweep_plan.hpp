@@ -125,22 +125,89 @@ inline TileSplit split_tiles(uint32_t nx, uint32_t ny, uint32_t nodes, uint32_t 
   return best;
 }
 
+// What the time of a step on rD2Q9 depends on besides the sizes: the storage,
+// walls or solid nodes, solid masks (link words), constant sources, a batch of
+// several domains.
+struct TileKind {
+  int es = 4;
+  bool bounded = false, links = false, sourced = false, batch = false;
+};
+
 // Time of a pass of `tiles` tiles of up to `blocks` nodes per thread and `steps`
-// steps with `slots` workgroups at once (us): a launch, and per round the first
-// loads, then each thread's nodes.  rD2Q9 FP32 with 512 threads, FP64 with 256
-// or 512; estimated / measured: FP32 2048 x 1024 58.5 / 57, 256 x 256 6.9 / 8.2,
-// FP64 2048 x 1024 (512 threads) 128 / 121, 64 x 32 (256 threads) 7.0 / 6.5.
-inline double tile_pass_us(uint64_t tiles, uint32_t blocks, uint32_t slots, int es, uint32_t threads, uint32_t steps) {
-  const double rounds = (double)((tiles + slots - 1) / slots);
-  const double load = es == 8 && threads <= 256 ? 0.8 : 0.9, step = es == 4 ? 0.75 : threads <= 256 ? 0.8 : 1.0;
-  return 1.5 + rounds * (1.5 + blocks * (load + steps * step));
+// steps on `cus` CUs (us): a launch, and per round of the workgroups that run at
+// once (two on a CU, one of 512 threads in FP64) their first loads, then each
+// thread's nodes; the last round is half paid for however few tiles it has, and
+// where each workgroup has a CU to itself it is the shorter.  Fitted to 650
+// measured passes of 3 and 4 steps (32 x 32 .. 2048 x 2048 nodes, single domains
+// and batches), 90% of them within 13%; estimated / measured, 4 steps: FP32
+// 2048 x 1024 54 / 49, with walls and force 78 / 67, 256 x 256 8.4 / 7.4, 64 x 32
+// 5.9 / 5.7; FP64 2048 x 1024 116 / 120, 64 x 32 6.2 / 5.8.
+inline double tile_pass_us(const TileKind& k, uint64_t tiles, uint32_t blocks, uint32_t cus, uint32_t threads,
+                           uint32_t steps) {
+  const bool alone = k.es == 8 && threads > 256;
+  const double x = (double)tiles / (alone ? cus : 2.0 * cus);
+  double rounds = std::max(1.0, 0.5 * (x + std::ceil(x)));
+  if (!alone && tiles <= cus) rounds = 0.65;
+  if (k.es == 4)
+    return 3.0 + rounds * (0.8 + blocks * (1.1 + steps * (0.63 + (k.bounded ? 0.28 : 0.0) + (k.sourced ? 0.19 : 0.0))));
+  if (!alone) return 2.8 + rounds * (0.85 + blocks * (0.83 + steps * (0.64 + (k.bounded ? 0.16 : 0.0))));
+  return rounds * (3.2 + blocks * (1.5 + steps * (0.66 + (k.bounded ? 0.13 : 0.0))));
 }
-// Is a pass faster than the single steps it stands for?  Those take a replayed
-// launch and their bytes at the rate of the memory-side cache (FP32 64 x 32 2.7
-// us, 512 x 512 4.5, 2048 x 1024 21; FP64 2048 x 1024 42).
-inline bool tiles_pay(double pass_us, uint64_t nodes, int es, uint32_t steps) {
-  const double single = 2.5 + (double)nodes * 18.0 * es / 8.4e6;
-  return pass_us < 0.9 * steps * single;
+
+// Time of a single step (us): a replayed launch and the bytes at the rate of the
+// memory-side cache, which falls from 9.6 TB/s as the state outgrows it (most
+// estimates within 10%; estimated / measured: FP32 64 x 32 2.4 / 2.4, 512 x 512
+// 4.4 / 4.2, 2048 x 1024 19.7 / 20.8; FP64 2048 x 1024 43 / 42, 2048 x 2048 97 / 99).
+inline double single_step_us(const TileKind& k, uint64_t nodes) {
+  const double mb = nodes * 18.0 * k.es / 1e6;
+  double us = 2.4 + mb / 9.6 + std::max(0.0, mb - 100.0) * (k.es == 4 ? 0.03 : 0.045) + std::max(0.0, mb - 400.0) * 0.045;
+  if (k.links)
+    us *= k.es == 4 ? 1.2 : 1.14;
+  else if (k.es == 4)
+    us *= 1.0 + (k.bounded ? 0.04 : 0.0) + (k.sourced ? 0.05 : 0.0);
+  return k.batch ? us + std::min(3.2, nodes / 8e4) : us;
+}
+
+// Is a pass of `steps` steps faster than as many single ones?  A pass loads and
+// exchanges its ring however few steps it takes, so one of four nearly always is
+// (us a step, single / passes of four: FP32 700 x 700 6.3 / 4.7, 1500 x 700 10.2 /
+// 8.2, with walls and force 6.9 / 6.6 and 11.4 / 11.0), one of three mostly
+// (5.3 and 9.2; 7.3 and 12.5), one of two only in batches of small domains (30 of
+// 64 x 48 6.5 / 3.9; FP32 1500 x 700 10.2 / 11.6, with walls and force 11.4 /
+// 15.9) and where launches are all there is: one tile per CU and node per thread
+// (calls of four steps 17.7 against 19.6 us).  The shorter the pass, the larger
+// the share of it that the estimates may be wrong by.
+inline bool tile_pass_pays(const TileKind& k, uint64_t tiles, uint32_t blocks, uint32_t cus, uint32_t threads,
+                           uint64_t nodes, uint32_t steps) {
+  const double margin = steps >= 4 ? 1.0 : steps == 3 ? 0.9 : 0.77;
+  const double pass = tile_pass_us(k, tiles, blocks, cus, threads, steps);
+  if (steps == 2 && blocks == 1 && tiles <= cus) return tile_pass_pays(k, tiles, blocks, cus, threads, nodes, 3);
+  return pass < margin * steps * single_step_us(k, nodes);
+}
+
+// The passes of a call that takes m (even) steps on the tile path: an even
+// number, so that the state ends in the buffer where single steps would leave
+// it.  Pairs of passes of four steps, then one pair for a remainder of six or
+// four where such passes pay; what is left is single steps.
+struct TileRule {
+  bool pays[5] = {};   // passes of that many steps
+};
+struct TileCall {
+  int fours = 0, last = 0, last_steps = 0;   // passes of four steps, then passes of last_steps
+  int passes() const { return fours + last; }
+  int steps() const { return 4 * fours + last * last_steps; }
+  int pass_steps(int k) const { return k < fours ? 4 : last_steps; }
+};
+inline TileCall tile_call(const TileRule& r, int m) {
+  TileCall c;
+  if (m < 4 || !r.pays[4]) return c;
+  c.fours = m / 8 * 2;
+  const int rest = m % 8;
+  if (rest >= 4 && r.pays[rest / 2]) {
+    c.last = 2;
+    c.last_steps = rest / 2;
+  }
+  return c;
 }
 
 }  // namespace rmrt

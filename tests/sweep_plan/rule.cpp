@@ -1,0 +1,91 @@
+// The rules that choose between single steps and passes of several steps.
+// Prints "ok" and exits 0.
+#include <stdio.h>
+
+#include "../../paper_2206_00366_amd/csrc/sweep_plan.hpp"
+
+using namespace rmrt;
+
+static int bad = 0;
+#define CHECK(cond, ...) \
+  if (!(cond)) { fprintf(stderr, __VA_ARGS__); fprintf(stderr, "\n"); bad = 1; }
+
+// a call's passes: pairs, of lengths that pay, never more steps than asked for
+static void calls() {
+  for (int mask = 0; mask < 8; ++mask) {
+    TileRule r;
+    for (int s = 2; s <= 4; ++s) r.pays[s] = (mask >> (s - 2)) & 1;
+    for (int m = 0; m <= 256; m += 2) {
+      const TileCall c = tile_call(r, m);
+      CHECK(c.fours % 2 == 0 && c.last % 2 == 0, "an odd number of passes for %d steps", m);
+      int steps = 0;
+      for (int k = 0; k < c.passes(); ++k) {
+        const int s = c.pass_steps(k);
+        CHECK(s >= 2 && s <= 4 && r.pays[s], "a pass of %d steps for %d (mask %d)", s, m, mask);
+        steps += s;
+      }
+      CHECK(steps == c.steps() && steps <= m && steps % 2 == 0, "%d of %d steps", steps, m);
+      if (r.pays[4]) CHECK(m - steps < 8, "%d of %d steps left over", m - steps, m);
+    }
+  }
+}
+
+// the tiles with the shortest pass, as the library chooses them
+static bool pays(const TileKind& k, uint32_t nx, uint32_t ny, uint32_t count, uint32_t steps) {
+  double best = 1e300;
+  bool out = false;
+  for (uint32_t twice = 0; twice < (k.es == 8 ? 2u : 1u); ++twice)
+    for (uint32_t blocks = 1; blocks <= 4; ++blocks) {
+      const uint32_t nt = (k.es == 8 ? 256u : 512u) << twice;
+      const TileSplit t = split_tiles(nx, ny, blocks * nt, 4);
+      if (t.cx == 0) continue;
+      const double us = tile_pass_us(k, count * t.tiles, blocks, 256, nt, 4);
+      if (us < best) {
+        best = us;
+        out = tile_pass_pays(k, count * t.tiles, blocks, 256, nt, (uint64_t)count * nx * ny, steps);
+      }
+    }
+  return out;
+}
+
+// measured time of passes of 4, 3 and 2 steps over that of as many single ones
+// (0: not told apart from the launches); a loss of more than 4% is not taken, a
+// gain of more than 40% is
+static void tiles() {
+  const struct { int es, bounded, links, sourced; uint32_t nx, ny; double of[5]; } rows[] = {
+      {4, 0, 0, 0, 64, 32, {0, 0, 0, 0.69, 0.59}},       {4, 0, 0, 0, 700, 700, {0, 0, 1.03, 0.85, 0.74}},
+      {4, 0, 0, 0, 1024, 1024, {0, 0, 1.13, 0.85, 0.74}}, {4, 0, 0, 0, 1500, 700, {0, 0, 1.14, 0.90, 0.80}},
+      {4, 0, 0, 0, 2048, 1024, {0, 0, 0.86, 0.68, 0.59}}, {4, 0, 0, 0, 2048, 2048, {0, 0, 1.11, 0.67, 0.60}},
+      {4, 1, 0, 1, 256, 256, {0, 0, 1.37, 1.01, 0.90}},   {4, 1, 0, 1, 700, 700, {0, 0, 1.34, 1.07, 0.96}},
+      {4, 1, 0, 1, 1500, 700, {0, 0, 1.40, 1.10, 0.96}},  {4, 1, 0, 1, 100, 3000, {0, 0, 1.47, 1.15, 1.03}},
+      {4, 1, 0, 1, 1024, 512, {0, 0, 1.32, 1.06, 0.95}},  {4, 1, 1, 1, 1500, 700, {0, 0, 1.19, 0.95, 0.82}},
+      {4, 1, 1, 1, 64, 32, {0, 0, 0, 0.63, 0.56}},        {4, 1, 1, 1, 2048, 1024, {0, 0, 0.96, 0.76, 0.63}},
+      {8, 0, 0, 0, 64, 32, {0, 0, 0, 0, 0.54}},           {8, 0, 0, 0, 700, 700, {0, 0, 1.14, 0.93, 0.81}},
+      {8, 1, 0, 0, 700, 700, {0, 0, 1.31, 1.04, 0.86}},   {8, 1, 0, 0, 1024, 512, {0, 0, 1.20, 0.98, 0.80}},
+      {8, 1, 0, 0, 2048, 1024, {0, 0, 1.10, 0.90, 0.76}}, {8, 0, 0, 0, 2048, 2048, {0, 0, 0.95, 0.75, 0.63}},
+  };
+  for (const auto& r : rows)
+    for (uint32_t s = 2; s <= 4; ++s) {
+      if (r.of[s] == 0) continue;
+      TileKind k;
+      k.es = r.es;
+      k.bounded = r.bounded;
+      k.links = r.links;
+      k.sourced = r.sourced;
+      const bool p = pays(k, r.nx, r.ny, 1, s);
+      if (r.of[s] > 1.04) CHECK(!p, "passes of %u steps taken on %u x %u, es %d, at %.2f", s, r.nx, r.ny, r.es, r.of[s]);
+      if (r.of[s] < 0.6) CHECK(p, "passes of %u steps refused on %u x %u, es %d, at %.2f", s, r.nx, r.ny, r.es, r.of[s]);
+    }
+  // batches of equal domains: 30 of 64 x 48 at 0.61, 0.50 and 0.43
+  TileKind k;
+  k.batch = true;
+  for (uint32_t s = 2; s <= 4; ++s) CHECK(pays(k, 64, 48, 30, s), "passes of %u steps refused on a batch", s);
+}
+
+int main() {
+  calls();
+  tiles();
+  if (bad) return 1;
+  printf("ok\n");
+  return 0;
+}
