@@ -1082,7 +1082,7 @@ int launch_tile_passes(StepLaunch a, int lattice, int storage, bool ab, const Ti
 // more.  A domain it does not serve, or memory that is not there, leaves the
 // single steps.
 int two_step_prepare(rmrt_ctx* c, hipStream_t s) {
-  if (c->two_step != 0) return RMRT_OK;
+  if (c->launch_set || c->two_step != 0) return RMRT_OK;   // (single steps only: asked again after rmrt_tune)
   if (c->p.lattice == RMRT_Q9) return tile_prepare(c, s);
   if (!two_step_model(c)) return RMRT_OK;   // asked again: source fields may be detached later
   c->two_step = -1;
@@ -2170,7 +2170,7 @@ void batch_advance(rmrt_batch* b, int n) {
 // The tile path of a batch of rD2Q9 domains, set up on its first call of four
 // steps or more.
 int batch_tile_prepare(rmrt_batch* b, hipStream_t s) {
-  if (b->tile_steps != 0) return RMRT_OK;
+  if (b->shape_set || b->tile_steps != 0) return RMRT_OK;   // (single steps only: asked again after the autotuner)
   b->tile_steps = -1;
   size_t bytes = 0;
   for (const rmrt_ctx* c : b->ctxs) {
