@@ -1026,6 +1026,19 @@ void* second_buffer(size_t bytes) {
   return p;
 }
 
+// The memory of a multi-step path: its work items and, for in-place domains, the
+// second buffers (second_bytes).  All of it or none.
+template <class Item>
+bool pass_memory(const std::vector<Item>& list, size_t second_bytes, Item** items, void** second) {
+  if (second_bytes > 0 && (*second = second_buffer(second_bytes)) == nullptr) return false;
+  if (hipMalloc(items, sizeof(Item) * list.size()) == hipSuccess) return true;
+  (void)hipGetLastError();
+  *items = nullptr;
+  if (*second) (void)hipFree(*second);
+  *second = nullptr;
+  return false;
+}
+
 StepLaunch two_step_launch(const rmrt_ctx* c) {
   StepLaunch a;
   std::memset(&a, 0, sizeof(a));
@@ -1048,16 +1061,12 @@ int tile_prepare(rmrt_ctx* c, hipStream_t s) {
     return RMRT_OK;
   }
   if (items.empty()) return RMRT_OK;
-  if (c->p.pattern == RMRT_AA) {
-    c->second = second_buffer((size_t)9 * c->hdom.ld * elem_size(c->p.storage));
-    if (!c->second) return RMRT_OK;
+  const bool in_place = c->p.pattern == RMRT_AA;
+  if (!pass_memory(items, in_place ? (size_t)9 * c->hdom.ld * elem_size(c->p.storage) : 0, &c->tile_items, &c->second))
+    return RMRT_OK;
+  if (in_place) {
     c->hdom.fb = c->second;
     HIP_TRY(hipMemcpyAsync(c->ddoms + c->dom, &c->hdom, sizeof(DomainDev), hipMemcpyHostToDevice, s));
-  }
-  if (hipMalloc(&c->tile_items, sizeof(TileItem) * items.size()) != hipSuccess) {
-    (void)hipGetLastError();
-    c->tile_items = nullptr;
-    return RMRT_OK;
   }
   HIP_TRY(hipMemcpyAsync(c->tile_items, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice, s));
   HIP_TRY(hipStreamSynchronize(s));
@@ -1102,17 +1111,11 @@ int two_step_prepare(rmrt_ctx* c, hipStream_t s) {
   } catch (const std::bad_alloc&) {
     return RMRT_OK;
   }
-  const size_t bytes = (size_t)q * c->hdom.ld * (size_t)es;
-  if (c->p.pattern == RMRT_AA) {
-    c->second = second_buffer(bytes);
-    if (!c->second) return RMRT_OK;
+  const bool in_place = c->p.pattern == RMRT_AA;
+  if (!pass_memory(items, in_place ? (size_t)q * c->hdom.ld * (size_t)es : 0, &c->items, &c->second)) return RMRT_OK;
+  if (in_place) {
     c->hdom.fb = c->second;
     HIP_TRY(hipMemcpyAsync(c->ddoms + c->dom, &c->hdom, sizeof(DomainDev), hipMemcpyHostToDevice, s));
-  }
-  if (hipMalloc(&c->items, sizeof(SweepItem) * items.size()) != hipSuccess) {
-    (void)hipGetLastError();
-    c->items = nullptr;
-    return RMRT_OK;
   }
   HIP_TRY(hipMemcpyAsync(c->items, items.data(), sizeof(SweepItem) * items.size(), hipMemcpyHostToDevice, s));
   HIP_TRY(hipStreamSynchronize(s));
@@ -2186,9 +2189,9 @@ int batch_tile_prepare(rmrt_batch* b, hipStream_t s) {
     return RMRT_OK;
   }
   if (items.empty()) return RMRT_OK;
-  if (b->pattern == RMRT_AA) {
-    b->second = second_buffer(bytes);
-    if (!b->second) return RMRT_OK;
+  const bool in_place = b->pattern == RMRT_AA;
+  if (!pass_memory(items, in_place ? bytes : 0, &b->tile_items, &b->second)) return RMRT_OK;
+  if (in_place) {
     char* at = (char*)b->second;
     for (size_t d = 0; d < b->ctxs.size(); ++d) {
       rmrt_ctx* c = b->ctxs[d];
@@ -2198,11 +2201,6 @@ int batch_tile_prepare(rmrt_batch* b, hipStream_t s) {
     }
     HIP_TRY(hipMemcpyAsync(b->ddoms, host.data(), sizeof(DomainDev) * host.size(), hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
-  }
-  if (hipMalloc(&b->tile_items, sizeof(TileItem) * items.size()) != hipSuccess) {
-    (void)hipGetLastError();
-    b->tile_items = nullptr;
-    return RMRT_OK;
   }
   HIP_TRY(hipMemcpyAsync(b->tile_items, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice, s));
   HIP_TRY(hipStreamSynchronize(s));
