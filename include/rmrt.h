@@ -28,10 +28,12 @@
  *   - Every device pointer is caller-owned device memory borrowed for the
  *     lifetime of the context; the library owns only the context, its device
  *     parameter block, reduction scratch, any captured graph and the second
- *     buffer that rmrt_step describes.
+ *     buffer that rmrt_step describes (with a work list and its pinned copy).
  *   - Every call is ordered on the caller's hipStream_t (passed as void*;
- *     NULL = the default stream).  Only rmrt_reduce and rmrt_residual
- *     synchronise that stream, to return their FP64 results to the host.
+ *     NULL = the default stream).  Of the calls that step or read a domain only
+ *     rmrt_reduce, rmrt_residual and rmrt_batch_residual synchronise that
+ *     stream, to return their FP64 results to the host; calls that set up
+ *     (creation, sources, checkpoints, launch shapes, preparing) may wait too.
  *   - Every function returns RMRT_OK (0) or a negative RMRT_E* code; a
  *     thread-local message is available from rmrt_last_error().  Nothing
  *     throws across the ABI.
@@ -277,7 +279,8 @@ int rmrt_set_source_fields(rmrt_ctx* ctx, const void* S, const void* F, void* st
  * steps.  An RMRT_AA domain gets a second population buffer for it on its
  * first call of four steps or more, owned by the context until rmrt_free;
  * without that memory (it takes at most an eighth of what is free) it steps
- * singly.  rD2Q9 domains and batches (raw-moment NSE, or NCDE without c_zero;
+ * singly, then and later.  That first call allocates but does not wait;
+ * rmrt_step_prepare does both ahead of it.  rD2Q9 domains and batches (raw-moment NSE, or NCDE without c_zero;
  * FP32, or FP64 without force and source; walls on both of two opposite faces
  * or none; solid masks) take four steps or more as passes of two to four steps
  * each on the same terms, in the lengths that are faster than single steps.
@@ -287,7 +290,8 @@ int rmrt_step(rmrt_ctx* ctx, int nsteps, void* stream);
 /*
  * Capture, instantiate and upload (on stream) the graphs that
  * rmrt_step(ctx, nsteps) will replay from the context's current step count,
- * without running them or advancing the state.  Optional: rmrt_step captures
+ * without running them or advancing the state, with the second buffer where
+ * their steps take one.  Optional: rmrt_step captures
  * a graph on its first use; calling this first keeps the capture out of a
  * timed region or a latency-sensitive loop.  RMRT_EINVAL for a domain of a
  * batch or nsteps < 0.
@@ -418,7 +422,7 @@ int rmrt_checkpoint_restore(rmrt_ctx* ctx, const void* src, void* stream);
  * whole number of 128-byte cache lines.  Invalidates the context's cached
  * graphs.  A context (or batch: rmrt_batch_set_config, _set_group_bytes,
  * _set_xcd_chunks) whose launch shape was set here takes single steps only,
- * in that shape; rmrt_tune chooses the shape of the single steps that remain.
+ * in that shape, and no second buffer; rmrt_tune chooses the shape of the single steps that remain.
  */
 #define RMRT_LAUNCH_XCD_ORDER 1
 #define RMRT_LAUNCH_PERSISTENT 2

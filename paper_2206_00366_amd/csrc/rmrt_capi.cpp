@@ -764,6 +764,7 @@ struct rmrt_ctx {
   bool launch_set = false;     // rmrt_set_launch was called: single steps of that shape only
   int two_step = 0;
   void* second = nullptr;
+  void* staged = nullptr;      // pinned: what the set-up sends to the device
   SweepItem* items = nullptr;
   TileItem* tile_items = nullptr;   // rD2Q9: several steps per pass (k_tile_steps) instead
   uint32_t nitems = 0, sweep_w = 0, tile_threads = 0;
@@ -850,6 +851,7 @@ void ctx_release(rmrt_ctx* c) {
   if (c->sprev) (void)hipFree(c->sprev);
   if (c->oob) (void)hipFree(c->oob);
   if (c->second) (void)hipFree(c->second);
+  if (c->staged) (void)hipHostFree(c->staged);
   if (c->items) (void)hipFree(c->items);
   if (c->tile_items) (void)hipFree(c->tile_items);
   if (c->owns_ddoms && c->ddoms) (void)hipFree(c->ddoms);
@@ -1026,17 +1028,39 @@ void* second_buffer(size_t bytes) {
   return p;
 }
 
-// The memory of a multi-step path: its work items and, for in-place domains, the
-// second buffers (second_bytes).  All of it or none.
+// The memory of a multi-step path: its work items, for in-place domains the second
+// buffers (second_bytes), and the pinned memory from which the items and the
+// parameter blocks of `domains` domains go to the device in stream order.  All of it
+// or none.
 template <class Item>
-bool pass_memory(const std::vector<Item>& list, size_t second_bytes, Item** items, void** second) {
+bool pass_memory(const std::vector<Item>& list, size_t second_bytes, size_t domains, Item** items, void** second,
+                 void** staged) {
   if (second_bytes > 0 && (*second = second_buffer(second_bytes)) == nullptr) return false;
-  if (hipMalloc(items, sizeof(Item) * list.size()) == hipSuccess) return true;
-  (void)hipGetLastError();
-  *items = nullptr;
+  const size_t bytes = sizeof(Item) * list.size();
+  if (hipMalloc(items, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    *items = nullptr;
+  } else if (hipHostMalloc(staged, sizeof(DomainDev) * domains + bytes, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    *staged = nullptr;
+  } else {
+    std::memcpy((char*)*staged + sizeof(DomainDev) * domains, list.data(), bytes);
+    return true;
+  }
+  if (*items) (void)hipFree(*items);
   if (*second) (void)hipFree(*second);
+  *items = nullptr;
   *second = nullptr;
   return false;
+}
+
+// Send the items and the parameter blocks (set in `staged` by then) on stream s.
+template <class Item>
+int send_pass_memory(void* staged, size_t domains, DomainDev* blocks, Item* items, size_t nitems, hipStream_t s) {
+  const size_t head = sizeof(DomainDev) * domains;
+  if (domains > 0) HIP_TRY(hipMemcpyAsync(blocks, staged, head, hipMemcpyHostToDevice, s));
+  HIP_TRY(hipMemcpyAsync(items, (char*)staged + head, sizeof(Item) * nitems, hipMemcpyHostToDevice, s));
+  return RMRT_OK;
 }
 
 StepLaunch two_step_launch(const rmrt_ctx* c) {
@@ -1048,6 +1072,17 @@ StepLaunch two_step_launch(const rmrt_ctx* c) {
   a.grid = c->nitems;
   a.sweep_w = c->sweep_w;
   return a;
+}
+
+// Hand an in-place context its second buffer, and send the set-up to the device.
+template <class Item>
+int send_second(rmrt_ctx* c, Item* items, size_t nitems, hipStream_t s) {
+  const bool in_place = c->second != nullptr;
+  if (in_place) {
+    c->hdom.fb = c->second;
+    std::memcpy(c->staged, &c->hdom, sizeof(DomainDev));
+  }
+  return send_pass_memory(c->staged, in_place ? 1 : 0, c->ddoms + c->dom, items, nitems, s);
 }
 
 // The tile path of an rD2Q9 context, set up on its first call of four steps or more.
@@ -1062,14 +1097,10 @@ int tile_prepare(rmrt_ctx* c, hipStream_t s) {
   }
   if (items.empty()) return RMRT_OK;
   const bool in_place = c->p.pattern == RMRT_AA;
-  if (!pass_memory(items, in_place ? (size_t)9 * c->hdom.ld * elem_size(c->p.storage) : 0, &c->tile_items, &c->second))
-    return RMRT_OK;
-  if (in_place) {
-    c->hdom.fb = c->second;
-    HIP_TRY(hipMemcpyAsync(c->ddoms + c->dom, &c->hdom, sizeof(DomainDev), hipMemcpyHostToDevice, s));
-  }
-  HIP_TRY(hipMemcpyAsync(c->tile_items, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  const size_t second_bytes = in_place ? (size_t)9 * c->hdom.ld * elem_size(c->p.storage) : 0;
+  if (!pass_memory(items, second_bytes, in_place ? 1 : 0, &c->tile_items, &c->second, &c->staged)) return RMRT_OK;
+  int rc = send_second(c, c->tile_items, items.size(), s);
+  if (rc != RMRT_OK) return rc;
   c->nitems = (uint32_t)items.size();
   c->two_step = 2;
   return RMRT_OK;
@@ -1112,13 +1143,10 @@ int two_step_prepare(rmrt_ctx* c, hipStream_t s) {
     return RMRT_OK;
   }
   const bool in_place = c->p.pattern == RMRT_AA;
-  if (!pass_memory(items, in_place ? (size_t)q * c->hdom.ld * (size_t)es : 0, &c->items, &c->second)) return RMRT_OK;
-  if (in_place) {
-    c->hdom.fb = c->second;
-    HIP_TRY(hipMemcpyAsync(c->ddoms + c->dom, &c->hdom, sizeof(DomainDev), hipMemcpyHostToDevice, s));
-  }
-  HIP_TRY(hipMemcpyAsync(c->items, items.data(), sizeof(SweepItem) * items.size(), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  const size_t second_bytes = in_place ? (size_t)q * c->hdom.ld * (size_t)es : 0;
+  if (!pass_memory(items, second_bytes, in_place ? 1 : 0, &c->items, &c->second, &c->staged)) return RMRT_OK;
+  int rc = send_second(c, c->items, items.size(), s);
+  if (rc != RMRT_OK) return rc;
   c->nitems = (uint32_t)items.size();
   c->sweep_w = plan.w;
   c->two_step = 1;
@@ -1183,8 +1211,11 @@ int graph_for(rmrt_ctx* c, int n, long long first, hipGraphExec_t* out, hipStrea
   const auto key = std::make_pair(n, (int)(first & 1));
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
+    const int paths = c->two_step;
     int rc = n >= 4 ? two_step_prepare(c, stream) : RMRT_OK;
     if (rc != RMRT_OK) return rc;
+    // a preparing call may be followed by steps on another stream
+    if (upload && c->two_step != paths) HIP_TRY(hipStreamSynchronize(stream));
     if (!c->cap) HIP_TRY(hipStreamCreateWithFlags(&c->cap, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
     rc = launch_steps(c, n, first, c->cap);
@@ -2044,6 +2075,7 @@ struct rmrt_batch {
   uint32_t ntile_items = 0, tile_w = 0, tile_threads = 0;
   TileRule tile_rule;
   void* second = nullptr;
+  void* staged = nullptr;      // pinned: what the set-up sends to the device
   Tile* res_blocks = nullptr;
   uint32_t nres_blocks = 0;
   ResidualState* res_states = nullptr;
@@ -2181,29 +2213,24 @@ int batch_tile_prepare(rmrt_batch* b, hipStream_t s) {
     bytes += ((size_t)9 * c->hdom.ld * elem_size(c->p.storage) + 255u) & ~(size_t)255u;
   }
   std::vector<TileItem> items;
-  std::vector<DomainDev> host;
   try {
     items = plan_tiles(b->ctxs, b->bc, b->force, (uint32_t)b->cus, &b->tile_w, &b->tile_threads, &b->tile_rule);
-    host.resize(b->ctxs.size());
   } catch (const std::bad_alloc&) {
     return RMRT_OK;
   }
   if (items.empty()) return RMRT_OK;
   const bool in_place = b->pattern == RMRT_AA;
-  if (!pass_memory(items, in_place ? bytes : 0, &b->tile_items, &b->second)) return RMRT_OK;
-  if (in_place) {
-    char* at = (char*)b->second;
-    for (size_t d = 0; d < b->ctxs.size(); ++d) {
-      rmrt_ctx* c = b->ctxs[d];
-      c->hdom.fb = at;
-      at += ((size_t)9 * c->hdom.ld * elem_size(c->p.storage) + 255u) & ~(size_t)255u;
-      host[d] = c->hdom;
-    }
-    HIP_TRY(hipMemcpyAsync(b->ddoms, host.data(), sizeof(DomainDev) * host.size(), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));
+  const size_t nblocks = in_place ? b->ctxs.size() : 0;
+  if (!pass_memory(items, in_place ? bytes : 0, nblocks, &b->tile_items, &b->second, &b->staged)) return RMRT_OK;
+  char* at = (char*)b->second;
+  for (size_t d = 0; d < nblocks; ++d) {
+    rmrt_ctx* c = b->ctxs[d];
+    c->hdom.fb = at;
+    at += ((size_t)9 * c->hdom.ld * elem_size(c->p.storage) + 255u) & ~(size_t)255u;
+    std::memcpy((DomainDev*)b->staged + d, &c->hdom, sizeof(DomainDev));
   }
-  HIP_TRY(hipMemcpyAsync(b->tile_items, items.data(), sizeof(TileItem) * items.size(), hipMemcpyHostToDevice, s));
-  HIP_TRY(hipStreamSynchronize(s));
+  int rc = send_pass_memory(b->staged, nblocks, b->ddoms, b->tile_items, items.size(), s);
+  if (rc != RMRT_OK) return rc;
   b->ntile_items = (uint32_t)items.size();
   b->tile_steps = 1;
   return RMRT_OK;
@@ -2249,8 +2276,10 @@ int batch_graph_for(rmrt_batch* b, int n, long long first, hipGraphExec_t* out, 
   const auto key = std::make_tuple(n, (int)(first & 1), b->cfg);
   auto it = b->graphs.find(key);
   if (it == b->graphs.end()) {
+    const int paths = b->tile_steps;
     int rc = n >= 4 ? batch_tile_prepare(b, stream) : RMRT_OK;
     if (rc != RMRT_OK) return rc;
+    if (upload && b->tile_steps != paths) HIP_TRY(hipStreamSynchronize(stream));
     if (!b->cap) HIP_TRY(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
     rc = batch_launch_steps(b, n, first, b->cap);
@@ -2360,6 +2389,7 @@ void batch_release(rmrt_batch* b) {
   if (b->ddoms) (void)hipFree(b->ddoms);
   if (b->tile_items) (void)hipFree(b->tile_items);
   if (b->second) (void)hipFree(b->second);
+  if (b->staged) (void)hipHostFree(b->staged);
   if (b->res_blocks) (void)hipFree(b->res_blocks);
   if (b->res_states) (void)hipFree(b->res_states);
   if (b->res_partials) (void)hipFree(b->res_partials);

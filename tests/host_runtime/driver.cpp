@@ -208,9 +208,27 @@ static void out_of_memory() {
   }
 }
 
+// The first call of four steps or more waits for nothing; the preparing call, after
+// which steps may come on any stream, does.
+static void no_wait() {
+  for (const Form& fm : forms) {
+    const std::string where = fm.name;
+    Runner r(fm), prepared(fm);
+    waits = 0;
+    CHECK(r.passes(8));
+    CHECK(waits == 0);
+    CHECK((prepared.c ? rmrt_step_prepare(prepared.c, 8, nullptr) : rmrt_batch_step_prepare(prepared.b, 8, nullptr)) == RMRT_OK);
+    CHECK(waits > 0);
+    waits = 0;
+    CHECK(prepared.step(8) == RMRT_OK);
+    CHECK(waits == 0);
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string s = argc > 1 ? argv[1] : "";
   if (s == "out_of_memory") out_of_memory();
+  else if (s == "no_wait") no_wait();
   else return fprintf(stderr, "unknown scenario\n"), 1;
   printf("ok\n");
   return 0;

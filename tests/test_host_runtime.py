@@ -38,3 +38,7 @@ def run(exe, scenario):
 
 def test_a_failed_set_up_leaves_single_steps_and_no_memory(driver):
     run(driver, "out_of_memory")
+
+
+def test_the_first_call_waits_for_nothing(driver):
+    run(driver, "no_wait")
