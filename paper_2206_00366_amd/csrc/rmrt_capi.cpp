@@ -1202,6 +1202,21 @@ int launch_steps(rmrt_ctx* c, int n, long long first, hipStream_t s) {
   return RMRT_OK;
 }
 
+// While the launch shapes of single steps are timed the flag that keeps a context
+// (or batch) on them is set; on every way out it is `after`, or what it was
+// before unless `after` was set, and the graphs captured meanwhile are gone.
+template <class Map>
+struct SingleSteps {
+  bool& flag;
+  Map& graphs;
+  bool after;
+  SingleSteps(bool& f, Map& g) : flag(f), graphs(g), after(f) { flag = true; }
+  ~SingleSteps() {
+    flag = after;
+    drop_graphs(graphs);
+  }
+};
+
 constexpr int kGraphChunk = 256;
 
 // The graph of n launches starting at step `first`, cached by (n, parity of
@@ -1826,6 +1841,7 @@ int rmrt_tune(rmrt_ctx* c, int steps, void* stream, int* blocks_per_cu) {
   hipEvent_t e0 = ev.e0, e1 = ev.e1;
   int best = kDefaultBlocksPerCU, best_flags = 0;
   float best_ms = 1e30f;
+  SingleSteps<decltype(c->graphs)> single(c->launch_set, c->graphs);
   const int nbuf = buffer_offsets_apply(c) ? 2 : 1;
   const int nchunk = rows_straddle_lines(c->p) ? 2 : 1;
   for (int chunk = 0; chunk < nchunk; ++chunk)
@@ -1853,7 +1869,7 @@ int rmrt_tune(rmrt_ctx* c, int steps, void* stream, int* blocks_per_cu) {
   }
   if (blocks_per_cu) *blocks_per_cu = best;
   const int rc = rmrt_set_launch(c, best, best_flags);
-  c->launch_set = false;   // the shape of the single steps; fours of steps stay on the two-step path
+  if (rc == RMRT_OK) single.after = false;   // the shape of the single steps; fours of steps stay on the two-step path
   return rc;
 }
 
@@ -2538,7 +2554,7 @@ int rmrt_batch_autotune(rmrt_batch* b, int steps, void* stream, int* chosen) {
   HIP_TRY(hipEventCreate(&ev.e0));
   HIP_TRY(hipEventCreate(&ev.e1));
   hipEvent_t e0 = ev.e0, e1 = ev.e1;
-  b->shape_set = true;   // the shapes of single steps are timed
+  SingleSteps<decltype(b->graphs)> single(b->shape_set, b->graphs);
   int best = -1;
   float best_ms = 1e30f;
   for (int cfg = 0; cfg < kNumTileShapes; ++cfg) {
@@ -2606,8 +2622,7 @@ int rmrt_batch_autotune(rmrt_batch* b, int steps, void* stream, int* chosen) {
     }
     b->xcd_chunks = mode_ms[1] <= mode_ms[0] ? 1 : 0;
   }
-  b->shape_set = false;   // tile passes, where the batch has them, stay the faster form
-  drop_graphs(b->graphs);
+  single.after = false;   // tile passes, where the batch has them, stay the faster form
   if (chosen) *chosen = best;
   return RMRT_OK;
 }

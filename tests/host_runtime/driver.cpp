@@ -225,10 +225,29 @@ static void no_wait() {
   }
 }
 
+// Tuning that fails leaves a context on passes, or on the single steps that it was
+// kept on; tuning that ends puts it on passes.
+static void failed_tuning() {
+  for (const Form& fm : forms)
+    for (int pinned = 0; pinned < 2; ++pinned)
+      for (int k : {1, 3, 0}) {
+        const std::string where = std::string(fm.name) + (pinned ? ", pinned" : "") + ", event " + std::to_string(k);
+        Runner r(fm);
+        if (pinned) CHECK(r.pin() == RMRT_OK);
+        event_waits = 0;
+        fail_event_at = k;
+        CHECK((r.tune() == RMRT_OK) == (k == 0));
+        fail_event_at = 0;
+        CHECK(r.passes(8) == (k == 0 || !pinned));
+        CHECK(r.passes(2) == false);
+      }
+}
+
 int main(int argc, char** argv) {
   const std::string s = argc > 1 ? argv[1] : "";
   if (s == "out_of_memory") out_of_memory();
   else if (s == "no_wait") no_wait();
+  else if (s == "failed_tuning") failed_tuning();
   else return fprintf(stderr, "unknown scenario\n"), 1;
   printf("ok\n");
   return 0;

@@ -42,3 +42,7 @@ def test_a_failed_set_up_leaves_single_steps_and_no_memory(driver):
 
 def test_the_first_call_waits_for_nothing(driver):
     run(driver, "no_wait")
+
+
+def test_failed_tuning_leaves_the_path_as_it_was(driver):
+    run(driver, "failed_tuning")
