@@ -299,6 +299,15 @@ int rmrt_step(rmrt_ctx* ctx, int nsteps, void* stream);
 int rmrt_step_prepare(rmrt_ctx* ctx, int nsteps, void* stream);
 
 /*
+ * *launches = how many times the kernels of rmrt_step(ctx, nsteps) would read and
+ * write the populations, from the context's current step count and as it is set
+ * up now: nsteps when it steps singly (also before its first call of four steps
+ * or more, or rmrt_step_prepare), fewer with passes of several steps.  Launches
+ * and changes nothing.  RMRT_EINVAL for a domain of a batch or nsteps < 0.
+ */
+int rmrt_step_launches(const rmrt_ctx* ctx, int nsteps, int* launches);
+
+/*
  * Macroscopic fields of the current state (eq. 2-4-1 / eq. 2-4-2):
  * rho (or phi) into rho_out[N]; u into u_out[d*N] SoA (may be NULL).
  * out_dtype RMRT_OUT_F64 or RMRT_OUT_F32.  Solid nodes are written as rho0, 0.
@@ -585,6 +594,9 @@ int rmrt_batch_step(rmrt_batch* b, int nsteps, void* stream);
  * of rmrt_batch_step(b, nsteps) for the current tile configuration and
  * domain groups, without running them. */
 int rmrt_batch_step_prepare(rmrt_batch* b, int nsteps, void* stream);
+
+/* rmrt_step_launches for a batch; a single step is a launch for each domain group. */
+int rmrt_batch_step_launches(const rmrt_batch* b, int nsteps, int* launches);
 
 /*
  * rmrt_residual for every domain of the batch with one host synchronisation:

@@ -1156,8 +1156,9 @@ int two_step_prepare(rmrt_ctx* c, hipStream_t s) {
 // Launch n steps from step `first`: single steps, and fours of steps as two
 // passes of the two-step kernel (out to the second buffer and back, so that
 // the state ends where single steps would leave it).  An in-place domain
-// enters the two-step path in its natural layout, i.e. at an even step.
-int launch_steps(rmrt_ctx* c, int n, long long first, hipStream_t s) {
+// enters the two-step path in its natural layout, i.e. at an even step.  With
+// `count` set nothing is launched: the launches are added to it.
+int launch_steps(rmrt_ctx* c, int n, long long first, hipStream_t s, int* count = nullptr) {
   const bool ab = c->p.pattern == RMRT_AB;
   const int lead = (!ab && (first & 1)) ? 1 : 0;
   const bool two = c->two_step == 1 && !c->launch_set && two_step_model(c);
@@ -1165,7 +1166,11 @@ int launch_steps(rmrt_ctx* c, int n, long long first, hipStream_t s) {
   if (c->two_step == 2 && !c->launch_set && tile_model(c, step_eq(c), step_force(c)))
     call = tile_call(c->tile_rule, (n - lead) & ~1);
   for (int i = 0; i < n;) {
-    if (call.passes() > 0 && i == lead) {
+    const bool tiles = call.passes() > 0 && i == lead, pair = two && i >= lead && n - i >= 4;
+    const int steps = tiles ? call.steps() : pair ? 4 : 1;
+    if (count) {
+      *count += tiles ? call.passes() : pair ? 2 : 1;
+    } else if (tiles) {
       StepLaunch a;
       std::memset(&a, 0, sizeof(a));
       a.two_step = 2;
@@ -1180,10 +1185,7 @@ int launch_steps(rmrt_ctx* c, int n, long long first, hipStream_t s) {
       a.stream = s;
       int rc = launch_tile_passes(a, c->p.lattice, c->p.storage, ab, call, first + i);
       if (rc != RMRT_OK) return rc;
-      i += call.steps();
-      continue;
-    }
-    if (two && i >= lead && n - i >= 4) {
+    } else if (pair) {
       StepLaunch a = two_step_launch(c);
       a.stream = s;
       const uint32_t cur = ab ? (uint32_t)((first + i) & 1) : 0u;
@@ -1192,12 +1194,11 @@ int launch_steps(rmrt_ctx* c, int n, long long first, hipStream_t s) {
         hipError_t e = dispatch_step(c->p.lattice, c->p.storage, a);
         if (e != hipSuccess) return fail(RMRT_EHIP, "two-step launch failed: %s", hipGetErrorString(e));
       }
-      i += 4;
     } else {
       int rc = launch_one_step(c, first + i, s);
       if (rc != RMRT_OK) return rc;
-      ++i;
     }
+    i += steps;
   }
   return RMRT_OK;
 }
@@ -1537,6 +1538,25 @@ int rmrt_step(rmrt_ctx* c, int nsteps, void* stream) {
     return RMRT_OK;
   }
   return step_impl(c, nsteps, s);
+}
+
+int rmrt_step_launches(const rmrt_ctx* c, int nsteps, int* launches) {
+  if (!c || !launches) return fail(RMRT_EINVAL, "NULL argument");
+  if (c->batch) return fail(RMRT_EINVAL, "domain belongs to a batch: use rmrt_batch_step_launches");
+  if (nsteps < 0) return fail(RMRT_EINVAL, "nsteps < 0");
+  *launches = 0;
+  const int most = c->p.check_every > 0 ? std::min(c->p.check_every, kGraphChunk) : kGraphChunk;
+  long long at = c->steps;
+  for (int left = nsteps, part = 0; left > 0;) {   // the graphs of rmrt_step: checked parts in chunks
+    if (part == 0) part = c->p.check_every > 0 ? std::min(left, c->p.check_every) : left;
+    const int k = std::min(part, most);
+    int rc = launch_steps(const_cast<rmrt_ctx*>(c), k, at, nullptr, launches);
+    if (rc != RMRT_OK) return rc;
+    at += k;
+    left -= k;
+    part -= k;
+  }
+  return RMRT_OK;
 }
 
 int rmrt_step_prepare(rmrt_ctx* c, int nsteps, void* stream) {
@@ -2253,12 +2273,16 @@ int batch_tile_prepare(rmrt_batch* b, hipStream_t s) {
 }
 
 // Launch n steps of every group from step `first`; rD2Q9 batches as tile
-// passes where they are set up.
-int batch_launch_steps(rmrt_batch* b, int n, long long first, hipStream_t s) {
+// passes where they are set up.  With `count` set the launches are only counted.
+int batch_launch_steps(rmrt_batch* b, int n, long long first, hipStream_t s, int* count = nullptr) {
   const bool ab = b->pattern == RMRT_AB;
   const int lead = (!ab && (first & 1)) ? 1 : 0;
   TileCall call;
   if (b->tile_steps == 1 && !b->shape_set) call = tile_call(b->tile_rule, (n - lead) & ~1);
+  if (count) {
+    *count += call.passes() + (n - call.steps()) * (int)b->groups.size();
+    return RMRT_OK;
+  }
   auto single = [&](int from, int to) {
     for (size_t gi = 0; gi < b->groups.size(); ++gi)
       for (int i = from; i < to; ++i) {
@@ -2527,6 +2551,21 @@ int rmrt_batch_step(rmrt_batch* b, int nsteps, void* stream) {
   if (!b) return fail(RMRT_EINVAL, "batch is NULL");
   if (nsteps < 0) return fail(RMRT_EINVAL, "nsteps < 0");
   return batch_step_impl(b, nsteps, (hipStream_t)stream);
+}
+
+int rmrt_batch_step_launches(const rmrt_batch* b, int nsteps, int* launches) {
+  if (!b || !launches) return fail(RMRT_EINVAL, "NULL argument");
+  if (nsteps < 0) return fail(RMRT_EINVAL, "nsteps < 0");
+  *launches = 0;
+  long long at = b->steps;
+  for (int left = nsteps; left > 0;) {
+    const int k = std::min(left, kGraphChunk);
+    int rc = batch_launch_steps(const_cast<rmrt_batch*>(b), k, at, nullptr, launches);
+    if (rc != RMRT_OK) return rc;
+    at += k;
+    left -= k;
+  }
+  return RMRT_OK;
 }
 
 int rmrt_batch_step_prepare(rmrt_batch* b, int nsteps, void* stream) {

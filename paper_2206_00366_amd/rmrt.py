@@ -81,6 +81,7 @@ _sig = {
     "rmrt_set_source_fields": (C.c_int, [_vp, _vp, _vp, _vp]),
     "rmrt_step": (C.c_int, [_vp, C.c_int, _vp]),
     "rmrt_step_prepare": (C.c_int, [_vp, C.c_int, _vp]),
+    "rmrt_step_launches": (C.c_int, [_vp, C.c_int, C.POINTER(C.c_int)]),
     "rmrt_moments": (C.c_int, [_vp, _vp, _vp, C.c_int, _vp]),
     "rmrt_populations": (C.c_int, [_vp, _vp, _vp]),
     "rmrt_reduce": (C.c_int, [_vp, C.POINTER(C.c_double), _vp]),
@@ -114,6 +115,7 @@ _sig = {
     "rmrt_step_local": (C.c_int, [_vp, C.c_int, _vp, C.c_int, _vp]),
     "rmrt_batch_step": (C.c_int, [_vp, C.c_int, _vp]),
     "rmrt_batch_step_prepare": (C.c_int, [_vp, C.c_int, _vp]),
+    "rmrt_batch_step_launches": (C.c_int, [_vp, C.c_int, C.POINTER(C.c_int)]),
     "rmrt_batch_residual": (C.c_int, [_vp, C.POINTER(C.c_double), _vp]),
     "rmrt_batch_free": (C.c_int, [_vp]),
     "rmrt_nn_conv_forward": (C.c_int, [_vp, _vp, _vp, _vp, _vp, _vp, C.c_int, C.c_int, C.c_int, C.c_int, C.c_int,
@@ -287,6 +289,12 @@ class Domain:
         """Capture the graphs of step(n) now (no steps are taken)."""
         _check(_lib.rmrt_step_prepare(self._ctx, int(n), _stream()), "rmrt_step_prepare")
 
+    def step_launches(self, n):
+        """Passes over the populations that step(n) would take as the context is set up now."""
+        k = C.c_int()
+        _check(_lib.rmrt_step_launches(self._ctx, int(n), C.byref(k)), "rmrt_step_launches")
+        return k.value
+
     def source_dtype(self):
         import torch
         return torch.float64 if self.params.storage == F64 else torch.float32
@@ -441,6 +449,12 @@ class Batch:
     def prepare(self, n):
         """Capture the graphs of step(n) now (no steps are taken)."""
         _check(_lib.rmrt_batch_step_prepare(self._b, int(n), _stream()), "rmrt_batch_step_prepare")
+
+    def step_launches(self, n):
+        """Launches that step(n) would take as the batch is set up now."""
+        k = C.c_int()
+        _check(_lib.rmrt_batch_step_launches(self._b, int(n), C.byref(k)), "rmrt_batch_step_launches")
+        return k.value
 
     def autotune(self, steps=10):
         ch = C.c_int()

@@ -158,6 +158,9 @@ struct Runner {
     int k;
     return c ? rmrt_tune(c, 2, nullptr, &k) : rmrt_batch_autotune(b, 2, nullptr, &k);
   }
+  int launches_of(int n, int* k) {
+    return c ? rmrt_step_launches(c, n, k) : rmrt_batch_step_launches(b, n, k);
+  }
   int pin() {
     if (b) return rmrt_batch_set_config(b, 0);
     int cap, fl;
@@ -243,11 +246,37 @@ static void failed_tuning() {
       }
 }
 
+// The launches that a context reports for a call are the ones that the call makes.
+static void counted_launches() {
+  for (const Form& fm : forms)
+    for (int pinned = 0; pinned < 2; ++pinned)
+      for (int n : {1, 2, 3, 4, 5, 6, 7, 8, 11, 13, 14, 20, 37, 100, 256, 300}) {
+        const std::string where = std::string(fm.name) + ", steps " + std::to_string(n);
+        Runner r(fm);
+        if (pinned) CHECK(r.pin() == RMRT_OK);
+        int k = -1;
+        CHECK(r.launches_of(n, &k) == RMRT_OK && k == n);   // nothing set up yet
+        CHECK((r.c ? rmrt_step_prepare(r.c, n, nullptr) : rmrt_batch_step_prepare(r.b, n, nullptr)) == RMRT_OK);
+        for (int again = 0; again < 2; ++again) {   // an even and, after odd calls, an odd step count
+          Runner same(fm);                          // (calls captured afresh)
+          if (pinned) CHECK(same.pin() == RMRT_OK);
+          if (again) CHECK(same.step(1) == RMRT_OK && r.step(1) == RMRT_OK);
+          launches.clear();
+          CHECK(same.step(n) == RMRT_OK);
+          CHECK(r.launches_of(n, &k) == RMRT_OK && k == (int)launches.size());
+          CHECK(!pinned || k == n);
+        }
+        CHECK(r.launches_of(-1, &k) == RMRT_EINVAL);
+        CHECK(r.launches_of(0, &k) == RMRT_OK && k == 0);
+      }
+}
+
 int main(int argc, char** argv) {
   const std::string s = argc > 1 ? argv[1] : "";
   if (s == "out_of_memory") out_of_memory();
   else if (s == "no_wait") no_wait();
   else if (s == "failed_tuning") failed_tuning();
+  else if (s == "counted_launches") counted_launches();
   else return fprintf(stderr, "unknown scenario\n"), 1;
   printf("ok\n");
   return 0;

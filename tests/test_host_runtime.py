@@ -46,3 +46,7 @@ def test_the_first_call_waits_for_nothing(driver):
 
 def test_failed_tuning_leaves_the_path_as_it_was(driver):
     run(driver, "failed_tuning")
+
+
+def test_reported_launches_are_the_ones_made(driver):
+    run(driver, "counted_launches")
