@@ -30,14 +30,15 @@ CONFIG_KEYS = ("threads", "tile_nodes", "blocks_per_cu", "persistent", "nodes_pe
 
 # HBM bytes per launch of the headline's single-step kernel from the rocprofv3 FETCH_SIZE
 # and WRITE_SIZE passes (profiles/k_step_q19_f32dev_256x256x128_pmc.md), scaled
-# by the counters of a plain copy of known size.  Keyed by the hash of the
-# kernel code the counters were taken on: any later code change reports null.
+# by the counters of a plain copy of known size.  Keyed by the hash of the code the
+# counters were taken on (the kernels and the choice of their patches): any
+# later code change reports null.
 MEASURED_TRAFFIC = {"691cb16803d1e347": 1275195792}
 # The same for launches of two steps: one read and one write of the populations,
 # and the rows that neighbouring slabs both read (1.08 x the algorithmic bytes).
 TWO_STEP_TRAFFIC = {"c5e8926fd6ca31ff": 1376897067}
 KERNEL_SOURCES = ["lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp", "lbm_launch.hpp", "lbm_two_step.hpp",
-                  "lbm_q19_f32.hip"]
+                  "lbm_q19_f32.hip", "sweep_plan.hpp"]
 
 
 def kernel_source_hash():
@@ -118,11 +119,17 @@ def run_single(torch, R, prm, rho, u, steps, warmup, solid=None, launch=None, se
     torch.cuda.synchronize()
     if settle_s > 0:
         settle(torch, R, settle_s)
-    wall, ev_ms = timed_steps(torch, dom.step, steps, warmup, prepare=dom.prepare)
+    passes = []
+
+    def prepare(k):
+        dom.prepare(k)
+        passes.append(dom.step_launches(k))   # of the timed call, as it is set up
+    wall, ev_ms = timed_steps(torch, dom.step, steps, warmup, prepare=prepare)
     red = dom.reduce()
     finite = all(math.isfinite(v) for v in red)
     if launch is not None:
         launch.update(dict(zip(("blocks_per_cu_cap", "flags"), dom.get_launch())))
+        launch["launches"] = passes[0]
     dom.close()
     del dom
     torch.cuda.empty_cache()
@@ -143,6 +150,26 @@ def lattice_entry(name, q, storage, N, steps, wall, ev_ms, note=None, extra_byte
     if note:
         e["note"] = note
     return e
+
+
+def headline_roofline(bytes_per_launch, launches, steps, ev_ms, launch):
+    """The roofline record of the headline's timed call of `steps` steps, which took
+    `launches` launches (the library's count): passes of two steps and single steps,
+    or single steps only where the two-step path was not set up.  Each launch reads
+    and writes the populations once."""
+    two = launches < steps
+    avg_s = ev_ms / launches * 1e-3
+    achieved = bytes_per_launch / avg_s / 1e9
+    src_hash = kernel_source_hash()
+    return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
+            "frac": round(achieved / HBM_PEAK_GBS, 4),
+            "traffic": (TWO_STEP_TRAFFIC if two else MEASURED_TRAFFIC).get(src_hash),
+            "kernel_source_hash": src_hash,
+            "kernel": "k_two_step<Q19, F32> (two steps per launch; k_step for the steps outside fours)" if two
+                      else "k_step<Q19, F32> (one step per launch)",
+            "algorithmic_bytes_per_launch": bytes_per_launch, "launches": launches, "steps": steps,
+            "avg_launch_us": round(avg_s * 1e6, 2),
+            "launch": dict(launch, workgroup=256, tile_nodes=256)}
 
 
 def copy_ceiling(torch, R, nbytes=2 << 30, reps=20):
@@ -305,20 +332,8 @@ def main():
     head = lattice_entry("rD3Q19 NSE TG 256x256x128 dz=2dx FP32-dev AA", 19, "f32dev", N_h, K, wall, ev_ms)
     head["finite"] = finite
     bytes_per_launch = 2 * 19 * 4 * N_h
-    # launches of the timed call, per graph of up to 256 steps: a single step when
-    # W left an odd step count, then two per four steps, then the rest singly;
-    # each reads and writes the populations once
-    launches = sum(k - 2 * ((k - (W & 1)) // 4) for k in [256] * (K // 256) + [K % 256] if k)
-    avg_launch_s = ev_ms / launches * 1e-3
-    achieved = bytes_per_launch / avg_launch_s / 1e9
-    src_hash = kernel_source_hash()
-    roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": TWO_STEP_TRAFFIC.get(src_hash),
-                "kernel_source_hash": src_hash,
-                "kernel": "k_two_step<Q19, F32> (two steps per launch; k_step for the steps outside fours)",
-                "algorithmic_bytes_per_launch": bytes_per_launch, "launches": launches, "steps": K,
-                "avg_launch_us": round(avg_launch_s * 1e6, 2),
-                "launch": dict(launch, workgroup=256, tile_nodes=256)}
+    launches = launch.pop("launches")
+    roofline = headline_roofline(bytes_per_launch, launches, K, ev_ms, launch)
 
     head["cold_gpu"] = {"MLUPS": round(N_h * K / wall_c / 1e6, 1), "ms_per_step": round(wall_c / K * 1e3, 4),
                         "avg_launch_us": round(ev_c / launches * 1e3, 2),
@@ -426,7 +441,7 @@ def main():
                                 "memory-side cache (MALL) from pass to pass: the most any reuse of data across "
                                 "steps through that cache could reach")
         out["mall_copy_ceiling"] = mall_ceiling
-        roofline["frac_of_copy_ceiling"] = round(achieved / ceiling["GBps"], 4)
+        roofline["frac_of_copy_ceiling"] = round(roofline["achieved"] / ceiling["GBps"], 4)
         roofline["note"] = ("achieved = algorithmic bytes / kernel time, one read and one write of the populations "
                             "per launch; where a launch takes two steps its slabs also read each other's edge rows "
                             "(traffic)")
