@@ -72,10 +72,11 @@ inline SweepPlan plan_sweep(uint32_t nx, uint32_t ny, uint32_t nz, int q, int es
 // estimate above is an upper one (most measured passes take 0.8 - 0.95 of
 // it), and where the two come close the single steps stay: they need no second
 // buffer.  Measured single / two-step, us a step: rD3Q19 FP32 64^3 12.9 /
-// 11.4 and 40 x 150 x 90 16.2 / 16.9 (not taken), 128 x 128 x 96 37.9 / 27.7,
-// 160^3 111 / 72, 256 x 256 x 128 196.5 / 133; rD3Q27 FP32 512 x 128 x 64
-// 146 / 152 and 223 x 116 x 100 89.7 / 92.2 (not taken), 192^3 258 / 183;
-// rD3Q19 FP64 128 x 128 x 96 78.8 / 60.9, 256 x 256 x 128 449 / 303.
+// 11.4 and 40 x 150 x 90 16.2 / 16.9 (not taken), 128 x 128 x 96 40 / 28,
+// 160^3 111 / 74, 256 x 256 x 128 196.5 / 135.5; rD3Q27 FP32 223 x 116 x 100
+// 89.7 / 92.2 (not taken), 512 x 128 x 64 147 / 127, 192^3 258 / 163; rD3Q19
+// FP64 128 x 128 x 96 85 / 62, 256 x 256 x 128 449 / 303.  Of 240 random sizes
+// of 2.5e5 to 8e6 nodes 130 are taken, at 0.63 to 0.98 of their single steps.
 inline bool sweep_pays(const SweepPlan& p, uint64_t nodes, int q, int es) {
   const double single = (double)nodes * 2.0 * q * es / 6.3e6 + 2.5;
   return 0.85 * p.us < 0.9 * 2.0 * single;

@@ -82,9 +82,30 @@ static void tiles() {
   for (uint32_t s = 2; s <= 4; ++s) CHECK(pays(k, 64, 48, 30, s), "passes of %u steps refused on a batch", s);
 }
 
+// two steps per pass in 3D: single step and step of a pass, us; a gain of more than
+// 20% is taken, a loss is not
+static void sweeps() {
+  const struct { int q, es; uint32_t nx, ny, nz; double single, two; } rows[] = {
+      {19, 4, 40, 150, 90, 16.2, 16.9},    {19, 4, 128, 128, 96, 40.1, 28.3},   {19, 4, 160, 160, 160, 111.7, 74.4},
+      {19, 4, 256, 256, 128, 196.5, 135.5}, {19, 4, 250, 203, 121, 155.3, 132.6}, {19, 4, 512, 140, 90, 158.6, 129.9},
+      {19, 4, 340, 128, 96, 105.9, 83.6},  {27, 4, 223, 116, 100, 89.7, 92.2},  {27, 4, 512, 128, 64, 147.1, 127.4},
+      {27, 4, 192, 192, 192, 258.6, 163.5}, {27, 4, 160, 160, 160, 152.3, 103.8}, {27, 4, 64, 256, 128, 70.7, 51.3},
+      {27, 4, 512, 140, 90, 240.0, 186.9}, {19, 8, 128, 128, 96, 85.1, 61.6},   {19, 8, 256, 256, 128, 449.0, 303.0},
+      {19, 8, 512, 128, 64, 212.7, 160.7}, {19, 8, 160, 160, 160, 211.8, 148.4}, {19, 8, 96, 96, 96, 46.6, 34.9},
+  };
+  for (const auto& r : rows) {
+    const uint32_t columns = r.q == 27 || r.es == 8 ? 1024 : 1536;
+    const SweepPlan p = plan_sweep(r.nx, r.ny, r.nz, r.q, r.es, columns, 256);
+    const bool pays = sweep_pays(p, (uint64_t)r.nx * r.ny * r.nz, r.q, r.es);
+    if (r.two > r.single) CHECK(!pays, "two steps per pass taken on %u x %u x %u, q %d, es %d", r.nx, r.ny, r.nz, r.q, r.es);
+    if (r.two < 0.83 * r.single) CHECK(pays, "two steps per pass refused on %u x %u x %u, q %d, es %d", r.nx, r.ny, r.nz, r.q, r.es);
+  }
+}
+
 int main() {
   calls();
   tiles();
+  sweeps();
   if (bad) return 1;
   printf("ok\n");
   return 0;
