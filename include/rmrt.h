@@ -641,7 +641,7 @@ int rmrt_nn_conv_forward(const void* x, const void* w, const float* bias, float*
 /* wt[ci][ky][kx][co] = w[co][2-ky][2-kx][ci]: backward-data is rmrt_nn_conv_forward with wt. */
 int rmrt_nn_flip_weights(const void* w, void* wt, int Cout, int Cin, void* stream);
 
-/* Scratch floats needed by rmrt_nn_conv_backward_weight. Host only. */
+/* Scratch floats needed by rmrt_nn_conv_backward_weight, for these sizes and any smaller B, H, W. Host only. */
 size_t rmrt_nn_wgrad_scratch_floats(int B, int H, int W, int Cin, int Cout);
 
 /*

@@ -12,7 +12,7 @@ namespace nn {
 hipError_t launch_conv(const uint16_t*, const uint16_t*, const float*, float*, uint16_t*, const float*, int, int, int,
                        int, int, int, int, hipStream_t);
 hipError_t launch_flip(const uint16_t*, uint16_t*, int, int, hipStream_t);
-size_t wgrad_partial_floats(int, int, int, int, int);
+size_t wgrad_scratch_floats(int, int, int, int, int);
 hipError_t launch_wgrad(const uint16_t*, const uint16_t*, int, int, int, int, int, int, float*, float*, float*, size_t,
                         hipStream_t);
 hipError_t launch_mse(const float*, int, const float*, const float*, long, int, uint16_t*, double*, float*, double*,
@@ -72,7 +72,7 @@ int rmrt_nn_flip_weights(const void* w, void* wt, int Cout, int Cin, void* strea
 
 size_t rmrt_nn_wgrad_scratch_floats(int B, int H, int W, int Cin, int Cout) {
   if (B < 1 || H < 1 || W < 1 || !ch_ok(Cin) || !ch_ok(Cout)) return 0;
-  return wgrad_partial_floats(B, H, W, Cin, Cout);
+  return wgrad_scratch_floats(B, H, W, Cin, Cout);
 }
 
 int rmrt_nn_conv_backward_weight(const void* x, const void* dy, int B, int H, int W, int Cin, int Cout, int dil,

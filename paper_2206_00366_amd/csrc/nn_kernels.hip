@@ -544,18 +544,22 @@ static long wgrad_blocks(int B, int H, int W, long* per_block) {
   *per_block = (items + kWgBlocks - 1) / kWgBlocks;
   return (items + *per_block - 1) / *per_block;
 }
-size_t wgrad_partial_floats(int B, int H, int W, int Cin, int Cout) {
-  long per = 0;
-  const size_t slots = (size_t)wgrad_blocks(B, H, W, &per) * (4 / ((Cin / 16) * (Cout / 16)));
-  return slots * ((size_t)9 * Cin * Cout + Cout);
+static size_t wgrad_partial_floats(long blocks, int Cin, int Cout) {
+  return (size_t)blocks * (4 / ((Cin / 16) * (Cout / 16))) * ((size_t)9 * Cin * Cout + Cout);
+}
+// Scratch for these sizes and all smaller ones (an even share can need fewer
+// workgroups for more segments: 257 for 513, 512 for 512).
+size_t wgrad_scratch_floats(int B, int H, int W, int Cin, int Cout) {
+  const long items = (long)B * H * ((W + kSeg - 1) / kSeg);
+  return wgrad_partial_floats(items < kWgBlocks ? items : kWgBlocks, Cin, Cout);
 }
 
 hipError_t launch_wgrad(const uint16_t* x, const uint16_t* dy, int B, int H, int W, int Cin, int Cout, int dil, float* dw,
                         float* db, float* part, size_t part_floats, hipStream_t s) {
-  if (wgrad_partial_floats(B, H, W, Cin, Cout) > part_floats) return hipErrorInvalidValue;
   const long items = (long)B * H * ((W + kSeg - 1) / kSeg);
   long per = 0;
   const long blocks = wgrad_blocks(B, H, W, &per);
+  if (wgrad_partial_floats(blocks, Cin, Cout) > part_floats) return hipErrorInvalidValue;
   const int slots = (int)blocks * (4 / ((Cin / 16) * (Cout / 16)));
   const int len = 9 * Cin * Cout;
   float* partb = part + (size_t)slots * len;
