@@ -159,7 +159,16 @@ __global__ void k_flip(const uint16_t* __restrict__ w, uint16_t* __restrict__ wt
 // from memory, one wave per tap and chunk, + 35 us for the sum of its partials
 // and + 213 us for db (its last sum was one thread per channel), 16 + 5 us now
 // together.
-constexpr int kSeg = 128, kWgBlocks = 512;
+// Rows of up to kNarrow pixels (FLAT) would leave most of a segment empty:
+// there a segment is kSeg consecutive pixels of the whole batch, whatever rows
+// and images they lie in, with one window per tap.  131072 pixels in rows of W,
+// 32 x 32 channels, dilation 1 / 2, by rows and flat (us, sums included): W = 1
+// 1206 / 753 and 25 / 25, 8 173 / 114 and 26 / 27, 32 50 / 34 and 26 / 26, 64
+// 34 / 25 and 25 / 25 (16 -> 16 channels 27 / 22 and 23 / 23: by rows).
+constexpr int kSeg = 128, kWgBlocks = 512, kNarrow = 32;
+inline long wgrad_items(int B, int H, int W) {
+  return W <= kNarrow ? ((long)B * H * W + kSeg - 1) / kSeg : (long)B * H * ((W + kSeg - 1) / kSeg);
+}
 __host__ __device__ inline bool wgrad_shared_window(int dil) { return dil > 0 && dil % 2 == 0 && dil <= 32; }
 __host__ __device__ inline int wgrad_window_pixels(int dil) {   // X pixels in LDS, a multiple of 2
   return wgrad_shared_window(dil) ? 3 * (kSeg + 2 * dil) : 9 * kSeg;
@@ -168,7 +177,7 @@ template <int CIN, int COUT>
 struct WgradSplit {
   static constexpr int MB = COUT / 16, NB = CIN / 16, KS = 4 / (MB * NB);
 };
-template <int CIN, int COUT>
+template <int CIN, int COUT, bool FLAT>
 __global__ void __launch_bounds__(256, 2)
     k_wgrad(const uint16_t* __restrict__ x, const uint16_t* __restrict__ dy, float* __restrict__ part,
             float* __restrict__ partb, int B, int H, int W, int dil, long items, long per_block) {
@@ -178,10 +187,11 @@ __global__ void __launch_bounds__(256, 2)
   uint32_t* const shx = sh + kSeg / 2 * COUT;        // [window pixels / 2][CIN]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = lane & 15, g = lane >> 4;
   const int blk = wave % (MB * NB), ks = wave / (MB * NB), a = blk / NB, c = blk % NB;
-  const bool shared = wgrad_shared_window(dil);
+  const bool shared = !FLAT && wgrad_shared_window(dil);
   const int win = shared ? kSeg + 2 * dil : kSeg;    // pixels of a window
   const int nwin = shared ? 3 : 9;
   const int nseg = (W + kSeg - 1) / kSeg;
+  const long P = (long)B * H * W;
   float4_t acc[9], accb = float4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int t = 0; t < 9; ++t) acc[t] = float4_t{0.f, 0.f, 0.f, 0.f};
@@ -204,18 +214,38 @@ __global__ void __launch_bounds__(256, 2)
   long it = (long)blockIdx.x * per_block;
   const long end = it + per_block < items ? it + per_block : items;
   for (; it < end; ++it) {
-    const long row = it / nseg;                      // b H + h
-    const int w0 = (int)(it - row * nseg) * kSeg;
-    const int h = (int)(row % H);
-    const int len = W - w0 < kSeg ? W - w0 : kSeg;
+    const long row = FLAT ? 0 : it / nseg;           // b H + h
+    const int w0 = FLAT ? 0 : (int)(it - row * nseg) * kSeg;
+    const int h = FLAT ? 0 : (int)(row % H);
+    const long p0 = FLAT ? it * kSeg : row * W + w0; // first pixel
+    const long left = FLAT ? P - p0 : (long)W - w0;
+    const int len = left < kSeg ? (int)left : kSeg;
     __syncthreads();                                 // the previous segment has been read
     for (int i = threadIdx.x; i < kSeg / 2 * (COUT / 8); i += 256) {
       const int pr = i / (COUT / 8), q = i % (COUT / 8);
-      const uint16_t* src = dy + (row * W + w0 + 2 * pr) * COUT + 8 * q;
+      const uint16_t* src = dy + (p0 + 2 * pr) * COUT + 8 * q;
       const u32x4_t lo = 2 * pr < len ? *(const bf16x8_mem*)src : zero;
       const u32x4_t hi = 2 * pr + 1 < len ? *(const bf16x8_mem*)(src + COUT) : zero;
       put(shy + pr * COUT + 8 * q, lo, hi);
     }
+    if constexpr (FLAT) {
+      for (int i = threadIdx.x; i < kSeg / 2 * (CIN / 8); i += 256) {
+        const int pr = i / (CIN / 8), q = i % (CIN / 8);
+        const long p = p0 + 2 * pr, r0 = p / W, r1 = (p + 1) / W;
+        const long h0 = r0 % H, h1 = r1 % H, x0 = p - r0 * W, x1 = p + 1 - r1 * W;
+        const bool ok0 = 2 * pr < len, ok1 = 2 * pr + 1 < len;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+          const long ty = (long)(t / 3 - 1) * dil, tx = (long)(t % 3 - 1) * dil;
+          const uint16_t* src = x + (p + ty * W + tx) * CIN + 8 * q;
+          const bool in0 = ok0 && h0 + ty >= 0 && h0 + ty < H && x0 + tx >= 0 && x0 + tx < W;
+          const bool in1 = ok1 && h1 + ty >= 0 && h1 + ty < H && x1 + tx >= 0 && x1 + tx < W;
+          const u32x4_t lo = in0 ? *(const bf16x8_mem*)src : zero;
+          const u32x4_t hi = in1 ? *(const bf16x8_mem*)(src + CIN) : zero;
+          put(shx + (t * (kSeg / 2) + pr) * CIN + 8 * q, lo, hi);
+        }
+      }
+    } else
     for (int i = threadIdx.x; i < nwin * (win / 2) * (CIN / 8); i += 256) {
       const int q = i % (CIN / 8), r = i / (CIN / 8), wi = r / (win / 2), pr = r - wi * (win / 2);
       const int ky = shared ? wi : wi / 3;
@@ -540,7 +570,7 @@ hipError_t launch_flip(const uint16_t* w, uint16_t* wt, int Cout, int Cin, hipSt
 
 // Workgroups of k_wgrad (row segments shared evenly) and their partial sums.
 static long wgrad_blocks(int B, int H, int W, long* per_block) {
-  const long items = (long)B * H * ((W + kSeg - 1) / kSeg);
+  const long items = wgrad_items(B, H, W);
   *per_block = (items + kWgBlocks - 1) / kWgBlocks;
   return (items + *per_block - 1) / *per_block;
 }
@@ -550,24 +580,29 @@ static size_t wgrad_partial_floats(long blocks, int Cin, int Cout) {
 // Scratch for these sizes and all smaller ones (an even share can need fewer
 // workgroups for more segments: 257 for 513, 512 for 512).
 size_t wgrad_scratch_floats(int B, int H, int W, int Cin, int Cout) {
-  const long items = (long)B * H * ((W + kSeg - 1) / kSeg);
+  const long items = wgrad_items(B, H, W);
   return wgrad_partial_floats(items < kWgBlocks ? items : kWgBlocks, Cin, Cout);
 }
 
 hipError_t launch_wgrad(const uint16_t* x, const uint16_t* dy, int B, int H, int W, int Cin, int Cout, int dil, float* dw,
                         float* db, float* part, size_t part_floats, hipStream_t s) {
-  const long items = (long)B * H * ((W + kSeg - 1) / kSeg);
+  const long items = wgrad_items(B, H, W);
+  const bool flat = W <= kNarrow;
   long per = 0;
   const long blocks = wgrad_blocks(B, H, W, &per);
   if (wgrad_partial_floats(blocks, Cin, Cout) > part_floats) return hipErrorInvalidValue;
   const int slots = (int)blocks * (4 / ((Cin / 16) * (Cout / 16)));
   const int len = 9 * Cin * Cout;
   float* partb = part + (size_t)slots * len;
-  const size_t lds = ((size_t)kSeg / 2 * Cout + (size_t)wgrad_window_pixels(dil) / 2 * Cin) * 4;
+  const size_t lds = ((size_t)kSeg / 2 * Cout + (size_t)(flat ? 9 * kSeg : wgrad_window_pixels(dil)) / 2 * Cin) * 4;
 #define WG_CASE(CI, CO)                                                                                             \
   if (Cin == CI && Cout == CO) {                                                                                    \
-    hipLaunchKernelGGL((k_wgrad<CI, CO>), dim3((unsigned)blocks), dim3(256), lds, s, x, dy, part, partb, B, H, W, dil, \
-                       items, per);                                                                                 \
+    if (flat)                                                                                                       \
+      hipLaunchKernelGGL((k_wgrad<CI, CO, true>), dim3((unsigned)blocks), dim3(256), lds, s, x, dy, part, partb, B, H, W, \
+                         dil, items, per);                                                                          \
+    else                                                                                                            \
+      hipLaunchKernelGGL((k_wgrad<CI, CO, false>), dim3((unsigned)blocks), dim3(256), lds, s, x, dy, part, partb, B, H, W, \
+                         dil, items, per);                                                                          \
   } else
   WG_CASE(16, 16) WG_CASE(16, 32) WG_CASE(32, 16) WG_CASE(32, 32) { return hipErrorInvalidValue; }
 #undef WG_CASE
