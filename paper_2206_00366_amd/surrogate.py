@@ -217,6 +217,11 @@ def run_to_steady(batch, tol=1e-6, check=50, max_steps=400_000, log=None, label=
     return steps, conv, wall, n, restarts
 
 
+def _device(device):
+    """A device argument as a torch.device; None is torch's default device."""
+    return torch.get_default_device() if device is None else torch.device(device)
+
+
 def _to_device(host, device):
     return host.to(device, non_blocking=True) if host.is_pinned() else host.to(device)
 
@@ -229,7 +234,8 @@ def _solid_tensor(geoms, device):
     if not geoms:
         raise ValueError("no geometries")
     shape = (geoms[0]["n"][1], geoms[0]["n"][0])
-    host = torch.empty((len(geoms),) + shape, dtype=torch.uint8, pin_memory=torch.device(device).type == "cuda")
+    device = _device(device)
+    host = torch.empty((len(geoms),) + shape, dtype=torch.uint8, pin_memory=device.type == "cuda")
     rows = host.numpy()
     for k, g in enumerate(geoms):
         solid = g["solid"].reshape(g["n"][1], g["n"][0])
@@ -241,7 +247,8 @@ def _solid_tensor(geoms, device):
 
 def geometry_tensors(geoms, device="cuda"):
     solid = _solid_tensor(geoms, device)
-    re = torch.empty(len(geoms), dtype=torch.float32, pin_memory=torch.device(device).type == "cuda")
+    device = _device(device)
+    re = torch.empty(len(geoms), dtype=torch.float32, pin_memory=device.type == "cuda")
     re.numpy()[:] = [g["Re"] for g in geoms]
     return solid, _to_device(re, device)
 

@@ -1,0 +1,17 @@
+"""The devices and values that the surrogate's geometry tensors take (host side)."""
+import numpy as np
+import torch
+
+from paper_2206_00366_amd import surrogate as S
+
+
+def geoms():
+    rng = np.random.default_rng(3)
+    return [dict(n=(7, 3), solid=rng.random(21) < 0.4, Re=10.5 + k) for k in range(3)]
+
+
+def test_no_device_is_the_default_device():
+    solid, re = S.geometry_tensors(geoms(), device=None)
+    want_solid, want_re = S.geometry_tensors(geoms(), device="cpu")
+    assert solid.device.type == re.device.type == "cpu"
+    assert torch.equal(solid, want_solid) and torch.equal(re, want_re)
