@@ -56,7 +56,8 @@ class Surrogate:
                 if biases is not None:
                     biases.append(flat[off + n:off + n + co])
             off += n + co
-            self.w32[l].copy_(torch.tensor(rng.standard_normal((co, 3, 3, ci)) * scale, dtype=torch.float32))
+            w = torch.tensor(rng.standard_normal((co, 3, 3, ci)) * scale, dtype=torch.float32, device="cpu")
+            self.w32[l].copy_(w)
             R.nn_to_bf16(self.w32[l], self.wbf[l])
             self.wt.append(torch.empty((ci, 3, 3, co), dtype=torch.bfloat16, device=device))
         self.t = 0
@@ -235,7 +236,7 @@ def _solid_tensor(geoms, device):
         raise ValueError("no geometries")
     shape = (geoms[0]["n"][1], geoms[0]["n"][0])
     device = _device(device)
-    host = torch.empty((len(geoms),) + shape, dtype=torch.uint8, pin_memory=device.type == "cuda")
+    host = torch.empty((len(geoms),) + shape, dtype=torch.uint8, device="cpu", pin_memory=device.type == "cuda")
     rows = host.numpy()
     for k, g in enumerate(geoms):
         solid = g["solid"].reshape(g["n"][1], g["n"][0])
@@ -248,7 +249,7 @@ def _solid_tensor(geoms, device):
 def geometry_tensors(geoms, device="cuda"):
     solid = _solid_tensor(geoms, device)
     device = _device(device)
-    re = torch.empty(len(geoms), dtype=torch.float32, pin_memory=device.type == "cuda")
+    re = torch.empty(len(geoms), dtype=torch.float32, device="cpu", pin_memory=device.type == "cuda")
     re.numpy()[:] = [g["Re"] for g in geoms]
     return solid, _to_device(re, device)
 

@@ -15,3 +15,11 @@ def test_no_device_is_the_default_device():
     want_solid, want_re = S.geometry_tensors(geoms(), device="cpu")
     assert solid.device.type == re.device.type == "cpu"
     assert torch.equal(solid, want_solid) and torch.equal(re, want_re)
+
+
+def test_a_default_device_elsewhere_changes_nothing():
+    want_solid, want_re = S.geometry_tensors(geoms(), device="cpu")
+    with torch.device("meta"):
+        solid, re = S.geometry_tensors(geoms(), device="cpu")
+    assert solid.device.type == re.device.type == "cpu"
+    assert torch.equal(solid, want_solid) and torch.equal(re, want_re)
