@@ -249,8 +249,9 @@ def _solid_tensor(geoms, device):
 def geometry_tensors(geoms, device="cuda"):
     solid = _solid_tensor(geoms, device)
     device = _device(device)
-    re = torch.empty(len(geoms), dtype=torch.float32, device="cpu", pin_memory=device.type == "cuda")
-    re.numpy()[:] = [g["Re"] for g in geoms]
+    values = np.array([g["Re"] for g in geoms], dtype=np.float32)
+    re = torch.empty(values.shape, dtype=torch.float32, device="cpu", pin_memory=device.type == "cuda")
+    np.copyto(re.numpy(), values)
     return solid, _to_device(re, device)
 
 

@@ -23,3 +23,11 @@ def test_a_default_device_elsewhere_changes_nothing():
         solid, re = S.geometry_tensors(geoms(), device="cpu")
     assert solid.device.type == re.device.type == "cpu"
     assert torch.equal(solid, want_solid) and torch.equal(re, want_re)
+
+
+def test_reynolds_numbers_of_any_shape():
+    made = geoms()
+    for g in made:
+        g["Re"] = np.array([g["Re"]])     # one value in an array, as a computed field gives it
+    _, re = S.geometry_tensors(made, device="cpu")
+    assert re.shape == (3, 1) and re.flatten().tolist() == [10.5, 11.5, 12.5]
