@@ -339,8 +339,8 @@ struct TwoStep {
   static constexpr int kColumns = L == LAT_Q27 ? 1 : 2;   // per thread
 };
 
-// Several steps per pass on rD2Q9 (lbm_tile_steps.hpp): the ring and so the most
-// steps of a pass, nodes per thread, threads of a workgroup (kTileThreads; FP64
+// Several steps per pass on rD2Q9 (lbm_tile_steps.hpp): the ring, which is also the
+// most steps of a pass (its exchanges need one node less), nodes per thread, threads of a workgroup (kTileThreads; FP64
 // also with twice as many) and workgroups that run on a CU (9 values per node
 // in LDS: 74 KB, or 147 KB).
 constexpr uint32_t kTileRing = 4, kTileNodes = 4;

@@ -2,11 +2,13 @@
 // (single ones and batches): temporal blocking over 2D tiles in LDS.
 //
 // A workgroup reads the natural state of a tile of columns x rows with a ring
-// of kRing nodes, takes up to kRing steps in LDS (a node's q values in
-// registers, pushed to the neighbours' LDS entries after each collision; the
-// outermost row and column of what is valid drops out with every step) and
-// writes the inner nodes' last pushes to another buffer.  Large domains move
-// their populations once for kRing steps, small ones launch once.
+// of kTileRing nodes, takes up to kTileRing steps in LDS (a node's q values in
+// registers, pushed to the neighbours' LDS entries after each collision but the
+// last; the outermost row and column of what is valid drops out with every such
+// exchange) and writes the inner nodes' last pushes to another buffer.  Large
+// domains move their populations once for four steps, small ones launch once.
+// A pass of s steps makes s - 1 exchanges and so needs a ring of s - 1: the ring
+// is one node wider than passes of four steps need.
 //
 // A bounced link returns to the node it left, in LDS as in memory.
 //

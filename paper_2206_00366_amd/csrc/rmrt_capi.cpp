@@ -2101,8 +2101,6 @@ struct rmrt_batch {
   // default), or never (mode 0)
   int xcd_chunks = 1;
   std::vector<uint8_t> group_chunked;
-  // residuals of all domains in one launch (below, res_*): the parts (one per workgroup), the
-  // domains' states (device copy and what it holds), the parts' partial sums
   // several steps per pass (rD2Q9): the tiles of all domains and the second
   // buffers of in-place ones; 0 not asked for yet, 1 there, -1 not served
   bool shape_set = false;      // the launch shape was set by hand: single steps of that shape only
@@ -2112,6 +2110,8 @@ struct rmrt_batch {
   TileRule tile_rule;
   void* second = nullptr;
   void* staged = nullptr;      // pinned: what the set-up sends to the device
+  // residuals of all domains in one launch: the parts (one per workgroup), the
+  // domains' states (device copy and what it holds), the parts' partial sums
   Tile* res_blocks = nullptr;
   uint32_t nres_blocks = 0;
   ResidualState* res_states = nullptr;

@@ -76,7 +76,7 @@ inline SweepPlan plan_sweep(uint32_t nx, uint32_t ny, uint32_t nz, int q, int es
 // 160^3 111 / 74, 256 x 256 x 128 196.5 / 135.5; rD3Q27 FP32 223 x 116 x 100
 // 89.7 / 92.2 (not taken), 512 x 128 x 64 147 / 127, 192^3 258 / 163; rD3Q19
 // FP64 128 x 128 x 96 85 / 62, 256 x 256 x 128 449 / 303.  Of 240 random sizes
-// of 2.5e5 to 8e6 nodes 130 are taken, at 0.63 to 0.98 of their single steps.
+// of 2.5e5 to 8e6 nodes 130 are taken, at 0.62 to 0.98 of their single steps.
 inline bool sweep_pays(const SweepPlan& p, uint64_t nodes, int q, int es) {
   const double single = (double)nodes * 2.0 * q * es / 6.3e6 + 2.5;
   return 0.85 * p.us < 0.9 * 2.0 * single;
