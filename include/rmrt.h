@@ -280,10 +280,11 @@ int rmrt_set_source_fields(rmrt_ctx* ctx, const void* S, const void* F, void* st
  * first call of four steps or more, owned by the context until rmrt_free;
  * without that memory (it takes at most an eighth of what is free) it steps
  * singly, then and later.  That first call allocates but does not wait;
- * rmrt_step_prepare does both ahead of it.  rD2Q9 domains and batches (raw-moment NSE, or NCDE without c_zero;
- * FP32, or FP64 without force and source; walls on both of two opposite faces
- * or none; solid masks) take four steps or more as passes of two to four steps
- * each on the same terms, in the lengths that are faster than single steps.
+ * rmrt_step_prepare does both ahead of it.  rD2Q9 domains and batches
+ * (raw-moment NSE, or NCDE without c_zero; FP32, or FP64 without force and
+ * source; walls on both of two opposite faces or none; solid masks) take four
+ * steps or more as passes of two to four steps each on the same terms, in the
+ * lengths that are faster than single steps.
  */
 int rmrt_step(rmrt_ctx* ctx, int nsteps, void* stream);
 
@@ -291,10 +292,9 @@ int rmrt_step(rmrt_ctx* ctx, int nsteps, void* stream);
  * Capture, instantiate and upload (on stream) the graphs that
  * rmrt_step(ctx, nsteps) will replay from the context's current step count,
  * without running them or advancing the state, with the second buffer where
- * their steps take one.  Optional: rmrt_step captures
- * a graph on its first use; calling this first keeps the capture out of a
- * timed region or a latency-sensitive loop.  RMRT_EINVAL for a domain of a
- * batch or nsteps < 0.
+ * their steps take one.  Optional: rmrt_step captures a graph on its first use;
+ * calling this first keeps the capture out of a timed region or a
+ * latency-sensitive loop.  RMRT_EINVAL for a domain of a batch or nsteps < 0.
  */
 int rmrt_step_prepare(rmrt_ctx* ctx, int nsteps, void* stream);
 

@@ -23,7 +23,7 @@
 // bytes and a step took 208-225 us (rD3Q19 FP32, 256 x 256 x 128; single
 // step 196.5), with 64 x 13 it took 171, with patches that span x (no ring
 // along x, whole rows end to end in memory: 256 x 4 inner columns) 140, and
-// with waves that hold ring columns only skipping stage 2 135.5 us.  The ring
+// with waves that hold ring columns only skipping stage 2 135 us.  The ring
 // and the two extra planes of a chunk are collided by more than one workgroup;
 // their reads mostly hit the L2.  rD3Q27 FP32 256 x 256 x 128: 293 -> 192 us a
 // step; rD3Q19 FP64: 449 -> 303 us.  FP16 storage gained nothing (106 -> 111 us:

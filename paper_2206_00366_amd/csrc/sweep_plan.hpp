@@ -73,7 +73,7 @@ inline SweepPlan plan_sweep(uint32_t nx, uint32_t ny, uint32_t nz, int q, int es
 // it), and where the two come close the single steps stay: they need no second
 // buffer.  Measured single / two-step, us a step: rD3Q19 FP32 64^3 12.9 /
 // 11.4 and 40 x 150 x 90 16.2 / 16.9 (not taken), 128 x 128 x 96 40 / 28,
-// 160^3 111 / 74, 256 x 256 x 128 196.5 / 135.5; rD3Q27 FP32 223 x 116 x 100
+// 160^3 111 / 74, 256 x 256 x 128 196.5 / 135; rD3Q27 FP32 223 x 116 x 100
 // 89.7 / 92.2 (not taken), 512 x 128 x 64 147 / 127, 192^3 258 / 163; rD3Q19
 // FP64 128 x 128 x 96 85 / 62, 256 x 256 x 128 449 / 303.  Of 240 random sizes
 // of 2.5e5 to 8e6 nodes 130 are taken, at 0.62 to 0.98 of their single steps.

@@ -60,9 +60,9 @@ static void tiles() {
       {4, 1, 0, 1, 1500, 700, {0, 0, 1.40, 1.10, 0.96}},  {4, 1, 0, 1, 100, 3000, {0, 0, 1.47, 1.15, 1.03}},
       {4, 1, 0, 1, 1024, 512, {0, 0, 1.32, 1.06, 0.95}},  {4, 1, 1, 1, 1500, 700, {0, 0, 1.19, 0.95, 0.82}},
       {4, 1, 1, 1, 64, 32, {0, 0, 0, 0.63, 0.56}},        {4, 1, 1, 1, 2048, 1024, {0, 0, 0.96, 0.76, 0.63}},
-      {8, 0, 0, 0, 64, 32, {0, 0, 0, 0, 0.54}},           {8, 0, 0, 0, 700, 700, {0, 0, 1.14, 0.93, 0.81}},
-      {8, 1, 0, 0, 700, 700, {0, 0, 1.31, 1.04, 0.86}},   {8, 1, 0, 0, 1024, 512, {0, 0, 1.20, 0.98, 0.80}},
-      {8, 1, 0, 0, 2048, 1024, {0, 0, 1.10, 0.90, 0.76}}, {8, 0, 0, 0, 2048, 2048, {0, 0, 0.95, 0.75, 0.63}},
+      {8, 0, 0, 0, 64, 32, {0, 0, 0, 0.57, 0.53}},           {8, 0, 0, 0, 700, 700, {0, 0, 1.16, 0.92, 0.83}},
+      {8, 1, 0, 0, 700, 700, {0, 0, 1.31, 1.03, 0.89}},   {8, 1, 0, 0, 1024, 512, {0, 0, 1.19, 0.94, 0.80}},
+      {8, 1, 0, 0, 2048, 1024, {0, 0, 1.11, 0.87, 0.75}}, {8, 0, 0, 0, 2048, 2048, {0, 0, 0.98, 0.73, 0.65}},
   };
   for (const auto& r : rows)
     for (uint32_t s = 2; s <= 4; ++s) {
@@ -76,7 +76,7 @@ static void tiles() {
       if (r.of[s] > 1.04) CHECK(!p, "passes of %u steps taken on %u x %u, es %d, at %.2f", s, r.nx, r.ny, r.es, r.of[s]);
       if (r.of[s] < 0.6) CHECK(p, "passes of %u steps refused on %u x %u, es %d, at %.2f", s, r.nx, r.ny, r.es, r.of[s]);
     }
-  // batches of equal domains: 30 of 64 x 48 at 0.61, 0.50 and 0.43
+  // batches of equal domains: 30 of about 64 x 48 at 0.60, 0.50 and 0.43
   TileKind k;
   k.batch = true;
   for (uint32_t s = 2; s <= 4; ++s) CHECK(pays(k, 64, 48, 30, s), "passes of %u steps refused on a batch", s);
