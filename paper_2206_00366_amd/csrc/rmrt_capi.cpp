@@ -956,23 +956,23 @@ bool tile_model(const rmrt_ctx* c, int eq, int force) {
   return c->p.n[0] >= 8 && c->p.n[1] >= 8;
 }
 
-static_assert(kTileRing == 4, "tile_call pairs passes of up to four steps");
-TileKind tile_kind(int storage, int bc, int force, size_t domains) {
+static_assert(kTileRing == 4, "tile_call takes passes of up to four steps");
+TileKind tile_kind(int storage, int bc, int force, bool batch) {
   TileKind k;
   k.es = (int)elem_size(storage);
   k.bounded = bc != 0;
   k.links = bc == 2;
   k.sourced = force != F_NONE;
-  k.batch = domains > 1;
+  k.batch = batch;
   return k;
 }
 
 // Tiles of the given domains, or none where single steps are faster: of the
 // workgroups and of the tile sizes of 1 .. 4 nodes per thread the ones with the
-// shortest pass; and the pass lengths that pay.
+// shortest pass; and what their passes take.
 std::vector<TileItem> plan_tiles(const std::vector<rmrt_ctx*>& doms, int bc, int force, uint32_t cus, uint32_t* width,
                                  uint32_t* threads, TileRule* rule) {
-  const TileKind kind = tile_kind(doms[0]->p.storage, bc, force, doms.size());
+  const TileKind kind = tile_kind(doms[0]->p.storage, bc, force, doms[0]->batch != nullptr);
   double best_us = 1e300;
   uint32_t best = 0;
   uint64_t nodes = 0;
@@ -988,18 +988,19 @@ std::vector<TileItem> plan_tiles(const std::vector<rmrt_ctx*>& doms, int bc, int
         tiles += t.tiles;
       }
       if (!fits) continue;
-      const double us = tile_pass_us(kind, tiles, blocks, cus, nt, kTileRing);
+      const double us =
+          tile_pass_us(kind, nodes, tiles, blocks, cus, nt, kTileRing) * (1.0 + kTileSizeBias * (kTileNodes - blocks));
       if (us < best_us) {
         best_us = us;
         best = blocks * nt;
         *threads = nt;
-        for (uint32_t n = 2; n <= kTileRing; ++n) rule->pays[n] = tile_pass_pays(kind, tiles, blocks, cus, nt, nodes, n);
+        *rule = tile_rule(kind, tiles, blocks, cus, nt, nodes);
       }
     }
   }
   std::vector<TileItem> items;
   *width = 0;
-  if (best == 0 || !rule->pays[kTileRing]) return items;
+  if (best == 0 || tile_call(*rule, 2 * (int)kTileRing).passes() == 0) return items;
   for (size_t d = 0; d < doms.size(); ++d) {
     const uint32_t nx = doms[d]->hdom.nx, ny = doms[d]->hdom.ny;
     const TileSplit t = split_tiles(nx, ny, best, kTileRing);

@@ -127,8 +127,7 @@ inline TileSplit split_tiles(uint32_t nx, uint32_t ny, uint32_t nodes, uint32_t 
 }
 
 // What the time of a step on rD2Q9 depends on besides the sizes: the storage,
-// walls or solid nodes, solid masks (link words), constant sources, a batch of
-// several domains.
+// walls or solid nodes, solid masks (link words), constant sources, a batch.
 struct TileKind {
   int es = 4;
   bool bounded = false, links = false, sourced = false, batch = false;
@@ -138,21 +137,27 @@ struct TileKind {
 // steps on `cus` CUs (us): a launch, and per round of the workgroups that run at
 // once (two on a CU, one of 512 threads in FP64) their first loads, then each
 // thread's nodes; the last round is half paid for however few tiles it has, and
-// where each workgroup has a CU to itself it is the shorter.  Fitted to 650
-// measured passes of 3 and 4 steps (32 x 32 .. 2048 x 2048 nodes, single domains
-// and batches), 90% of them within 13%; estimated / measured, 4 steps: FP32
+// where each workgroup has a CU to itself it is the shorter.  Two buffers that
+// the 256 MB memory-side cache does not hold bound short passes (3.2 TB/s).
+// Fitted to 650 measured passes of 3 and 4 steps (32 x 32 .. 2048 x 2048 nodes,
+// single domains and batches), 90% of them within 13%; estimated / measured, 4 steps: FP32
 // 2048 x 1024 54 / 49, with walls and force 78 / 67, 256 x 256 8.4 / 7.4, 64 x 32
 // 5.9 / 5.7; FP64 2048 x 1024 116 / 120, 64 x 32 6.2 / 5.8.
-inline double tile_pass_us(const TileKind& k, uint64_t tiles, uint32_t blocks, uint32_t cus, uint32_t threads,
-                           uint32_t steps) {
+inline double tile_pass_us(const TileKind& k, uint64_t nodes, uint64_t tiles, uint32_t blocks, uint32_t cus,
+                           uint32_t threads, uint32_t steps) {
   const bool alone = k.es == 8 && threads > 256;
   const double x = (double)tiles / (alone ? cus : 2.0 * cus);
   double rounds = std::max(1.0, 0.5 * (x + std::ceil(x)));
   if (!alone && tiles <= cus) rounds = 0.65;
+  double us;
   if (k.es == 4)
-    return 3.0 + rounds * (0.8 + blocks * (1.1 + steps * (0.63 + (k.bounded ? 0.28 : 0.0) + (k.sourced ? 0.19 : 0.0))));
-  if (!alone) return 2.8 + rounds * (0.85 + blocks * (0.83 + steps * (0.64 + (k.bounded ? 0.16 : 0.0))));
-  return rounds * (3.2 + blocks * (1.5 + steps * (0.66 + (k.bounded ? 0.13 : 0.0))));
+    us = 3.0 + rounds * (0.8 + blocks * (1.1 + steps * (0.63 + (k.bounded ? 0.28 : 0.0) + (k.sourced ? 0.19 : 0.0))));
+  else if (!alone)
+    us = 2.8 + rounds * (0.85 + blocks * (0.83 + steps * (0.64 + (k.bounded ? 0.16 : 0.0))));
+  else
+    us = rounds * (3.2 + blocks * (1.5 + steps * (0.66 + (k.bounded ? 0.13 : 0.0))));
+  const double mb = nodes * 18.0 * k.es / 1e6;
+  return mb > 256.0 ? std::max(us, mb / 3.2) : us;
 }
 
 // Time of a single step (us): a replayed launch and the bytes at the rate of the
@@ -161,7 +166,8 @@ inline double tile_pass_us(const TileKind& k, uint64_t tiles, uint32_t blocks, u
 // 4.4 / 4.2, 2048 x 1024 19.7 / 20.8; FP64 2048 x 1024 43 / 42, 2048 x 2048 97 / 99).
 inline double single_step_us(const TileKind& k, uint64_t nodes) {
   const double mb = nodes * 18.0 * k.es / 1e6;
-  double us = 2.4 + mb / 9.6 + std::max(0.0, mb - 100.0) * (k.es == 4 ? 0.03 : 0.045) + std::max(0.0, mb - 400.0) * 0.045;
+  double us = 2.4 + mb / 9.6 + std::max(0.0, mb - 100.0) * (k.es == 4 ? 0.03 : 0.045);
+  us += std::max(0.0, mb - 400.0) * 0.045;
   if (k.links)
     us *= k.es == 4 ? 1.2 : 1.14;
   else if (k.es == 4)
@@ -169,46 +175,61 @@ inline double single_step_us(const TileKind& k, uint64_t nodes) {
   return k.batch ? us + std::min(3.2, nodes / 8e4) : us;
 }
 
-// Is a pass of `steps` steps faster than as many single ones?  A pass loads and
-// exchanges its ring however few steps it takes, so one of four nearly always is
-// (us a step, single / passes of four: FP32 700 x 700 6.3 / 4.7, 1500 x 700 10.2 /
-// 8.2, with walls and force 6.9 / 6.6 and 11.4 / 11.0), one of three mostly
-// (5.3 and 9.2; 7.3 and 12.5), one of two only in batches of small domains (30 of
-// 64 x 48 6.5 / 3.9; FP32 1500 x 700 10.2 / 11.6, with walls and force 11.4 /
-// 15.9) and where launches are all there is: one tile per CU and node per thread
-// (calls of four steps 17.7 against 19.6 us).  The shorter the pass, the larger
-// the share of it that the estimates may be wrong by.
-inline bool tile_pass_pays(const TileKind& k, uint64_t tiles, uint32_t blocks, uint32_t cus, uint32_t threads,
-                           uint64_t nodes, uint32_t steps) {
-  const double margin = steps >= 4 ? 1.0 : steps == 3 ? 0.9 : 0.77;
-  const double pass = tile_pass_us(k, tiles, blocks, cus, threads, steps);
-  if (steps == 2 && blocks == 1 && tiles <= cus) return tile_pass_pays(k, tiles, blocks, cus, threads, nodes, 3);
-  return pass < margin * steps * single_step_us(k, nodes);
+// The passes that the tiles of a context can take, and single steps, by their
+// estimated time (us).  A pass loads and exchanges its ring however few steps it
+// takes: us a step, single / passes of four, three and two: FP32 700 x 700 6.3 /
+// 4.7, 5.3, 6.5, 1500 x 700 10.2 / 8.1, 9.2, 11.6, with walls and force 11.4 / 11.0,
+// 12.5, 15.9; a batch of 30 of 64 x 48 6.5 / 2.8, 3.3, 3.9.  The shorter the pass,
+// the larger its share that the estimate may be wrong by: passes of four are
+// taken up to 1.05 of their single steps, of three below 0.96, of two below 0.87
+// (or where launches are all there is, with a tile of one node per thread on each
+// CU: calls of four steps 17.7 against 19.6 us).
+struct TileRule {
+  double pass[5] = {}, single = 0.0;   // a pass of 2 .. 4 steps, weighted as above; a single step
+};
+inline TileRule tile_rule(const TileKind& k, uint64_t tiles, uint32_t blocks, uint32_t cus, uint32_t threads,
+                          uint64_t nodes) {
+  TileRule r;
+  r.single = single_step_us(k, nodes);
+  const double weight[5] = {0.0, 0.0, 1.15, 1.04, 0.95};
+  for (uint32_t n = 2; n <= 4; ++n) r.pass[n] = weight[n] * tile_pass_us(k, nodes, tiles, blocks, cus, threads, n);
+  if (blocks == 1 && tiles <= cus) r.pass[2] = std::min(r.pass[2], 1.9 * r.single);
+  return r;
 }
 
-// The passes of a call that takes m (even) steps on the tile path: an even
-// number, so that the state ends in the buffer where single steps would leave
-// it.  Pairs of passes of four steps, then one pair for a remainder of six or
-// four where such passes pay; what is left is single steps.
-struct TileRule {
-  bool pays[5] = {};   // passes of that many steps
-};
+// The passes of a call that takes m (even) steps on the tile path: an even number
+// of each length, so that the state ends in the buffer where single steps would
+// leave it; single steps for what is left.  Of the splits with up to four passes
+// of three and two of two the one with the shortest estimated time.
 struct TileCall {
-  int fours = 0, last = 0, last_steps = 0;   // passes of four steps, then passes of last_steps
-  int passes() const { return fours + last; }
-  int steps() const { return 4 * fours + last * last_steps; }
-  int pass_steps(int k) const { return k < fours ? 4 : last_steps; }
+  int fours = 0, threes = 0, twos = 0;
+  int passes() const { return fours + threes + twos; }
+  int steps() const { return 4 * fours + 3 * threes + 2 * twos; }
+  int pass_steps(int k) const { return k < fours ? 4 : k < fours + threes ? 3 : 2; }
 };
 inline TileCall tile_call(const TileRule& r, int m) {
-  TileCall c;
-  if (m < 4 || !r.pays[4]) return c;
-  c.fours = m / 8 * 2;
-  const int rest = m % 8;
-  if (rest >= 4 && r.pays[rest / 2]) {
-    c.last = 2;
-    c.last_steps = rest / 2;
-  }
-  return c;
+  TileCall best;
+  double best_us = m * r.single;
+  for (int threes = 0; threes <= 4; threes += 2)
+    for (int twos = 0; twos <= 2; twos += 2) {
+      TileCall c;
+      c.threes = threes;
+      c.twos = twos;
+      if (c.steps() > m) continue;
+      if (r.pass[4] < 4.0 * r.single) c.fours = (m - c.steps()) / 8 * 2;
+      const double us = c.fours * r.pass[4] + threes * r.pass[3] + twos * r.pass[2] + (m - c.steps()) * r.single;
+      if (us < best_us) {
+        best_us = us;
+        best = c;
+      }
+    }
+  return best;
 }
+
+// How much longer a split may be estimated and still be preferred for each node
+// per thread that its tiles have more than another's: larger tiles have less ring
+// (700 x 700 FP32, 4 nodes per thread 18.7 us a pass, estimated 18.3; 2 nodes
+// 19.8, estimated 17.9).
+constexpr double kTileSizeBias = 0.02;
 
 }  // namespace rmrt

@@ -10,42 +10,57 @@ static int bad = 0;
 #define CHECK(cond, ...) \
   if (!(cond)) { fprintf(stderr, __VA_ARGS__); fprintf(stderr, "\n"); bad = 1; }
 
-// a call's passes: pairs, of lengths that pay, never more steps than asked for
+// a call's passes: an even number of each length, lengths that pay, never more
+// steps than asked for, and no split of the same kind that is estimated shorter
 static void calls() {
-  for (int mask = 0; mask < 8; ++mask) {
+  for (int mask = 0; mask < 27; ++mask) {
     TileRule r;
-    for (int s = 2; s <= 4; ++s) r.pays[s] = (mask >> (s - 2)) & 1;
+    r.single = 1.0;
+    for (int s = 2, v = mask; s <= 4; ++s, v /= 3) r.pass[s] = s * (v % 3 == 0 ? 0.5 : v % 3 == 1 ? 0.9 : 1.2);
     for (int m = 0; m <= 256; m += 2) {
       const TileCall c = tile_call(r, m);
-      CHECK(c.fours % 2 == 0 && c.last % 2 == 0, "an odd number of passes for %d steps", m);
+      CHECK(c.fours % 2 == 0 && c.threes % 2 == 0 && c.twos % 2 == 0, "an odd number of passes for %d steps", m);
       int steps = 0;
+      double us = 0.0;
       for (int k = 0; k < c.passes(); ++k) {
         const int s = c.pass_steps(k);
-        CHECK(s >= 2 && s <= 4 && r.pays[s], "a pass of %d steps for %d (mask %d)", s, m, mask);
+        CHECK(s >= 2 && s <= 4 && r.pass[s] < s, "a pass of %d steps for %d (mask %d)", s, m, mask);
         steps += s;
+        us += r.pass[s];
       }
       CHECK(steps == c.steps() && steps <= m && steps % 2 == 0, "%d of %d steps", steps, m);
-      if (r.pays[4]) CHECK(m - steps < 8, "%d of %d steps left over", m - steps, m);
+      us += m - steps;
+      if (r.pass[4] < 4) CHECK(m - steps < 8, "%d of %d steps left over", m - steps, m);
+      for (int f = 0; 8 * f <= m; ++f)
+        for (int t = 0; 8 * f + 6 * t <= m && t <= 2; ++t)
+          for (int w = 0; 8 * f + 6 * t + 4 * w <= m && w <= 1; ++w)
+            CHECK(us <= 2 * (f * r.pass[4] + t * r.pass[3] + w * r.pass[2]) + (m - 8 * f - 6 * t - 4 * w) + 1e-9,
+                  "a shorter split of %d steps (mask %d)", m, mask);
     }
   }
 }
 
-// the tiles with the shortest pass, as the library chooses them
-static bool pays(const TileKind& k, uint32_t nx, uint32_t ny, uint32_t count, uint32_t steps) {
+// the rule of the tiles that the library chooses
+static TileRule rule_of(const TileKind& k, uint32_t nx, uint32_t ny, uint32_t count) {
   double best = 1e300;
-  bool out = false;
+  TileRule out;
   for (uint32_t twice = 0; twice < (k.es == 8 ? 2u : 1u); ++twice)
     for (uint32_t blocks = 1; blocks <= 4; ++blocks) {
       const uint32_t nt = (k.es == 8 ? 256u : 512u) << twice;
       const TileSplit t = split_tiles(nx, ny, blocks * nt, 4);
       if (t.cx == 0) continue;
-      const double us = tile_pass_us(k, count * t.tiles, blocks, 256, nt, 4);
+      const uint64_t nodes = (uint64_t)count * nx * ny, tiles = count * t.tiles;
+      const double us = tile_pass_us(k, nodes, tiles, blocks, 256, nt, 4) * (1.0 + kTileSizeBias * (4 - blocks));
       if (us < best) {
         best = us;
-        out = tile_pass_pays(k, count * t.tiles, blocks, 256, nt, (uint64_t)count * nx * ny, steps);
+        out = tile_rule(k, tiles, blocks, 256, nt, nodes);
       }
     }
   return out;
+}
+static bool pays(const TileKind& k, uint32_t nx, uint32_t ny, uint32_t count, uint32_t steps) {
+  const TileRule r = rule_of(k, nx, ny, count);
+  return r.pass[steps] < steps * r.single;
 }
 
 // measured time of passes of 4, 3 and 2 steps over that of as many single ones
@@ -57,7 +72,7 @@ static void tiles() {
       {4, 0, 0, 0, 1024, 1024, {0, 0, 1.13, 0.85, 0.74}}, {4, 0, 0, 0, 1500, 700, {0, 0, 1.14, 0.90, 0.80}},
       {4, 0, 0, 0, 2048, 1024, {0, 0, 0.86, 0.68, 0.59}}, {4, 0, 0, 0, 2048, 2048, {0, 0, 1.11, 0.67, 0.60}},
       {4, 1, 0, 1, 256, 256, {0, 0, 1.37, 1.01, 0.90}},   {4, 1, 0, 1, 700, 700, {0, 0, 1.34, 1.07, 0.96}},
-      {4, 1, 0, 1, 1500, 700, {0, 0, 1.40, 1.10, 0.96}},  {4, 1, 0, 1, 100, 3000, {0, 0, 1.47, 1.15, 1.03}},
+      {4, 1, 0, 1, 1500, 700, {0, 0, 1.40, 1.10, 0.96}},  {4, 1, 0, 1, 100, 3000, {0, 0, 1.22, 1.00, 0.89}},
       {4, 1, 0, 1, 1024, 512, {0, 0, 1.32, 1.06, 0.95}},  {4, 1, 1, 1, 1500, 700, {0, 0, 1.19, 0.95, 0.82}},
       {4, 1, 1, 1, 64, 32, {0, 0, 0, 0.63, 0.56}},        {4, 1, 1, 1, 2048, 1024, {0, 0, 0.96, 0.76, 0.63}},
       {8, 0, 0, 0, 64, 32, {0, 0, 0, 0.57, 0.53}},           {8, 0, 0, 0, 700, 700, {0, 0, 1.16, 0.92, 0.83}},
