@@ -36,7 +36,7 @@ CONFIG_KEYS = ("threads", "tile_nodes", "blocks_per_cu", "persistent", "nodes_pe
 MEASURED_TRAFFIC = {"691cb16803d1e347": 1275195792}
 # The same for launches of two steps: one read and one write of the populations,
 # and the rows that neighbouring slabs both read (1.08 x the algorithmic bytes).
-TWO_STEP_TRAFFIC = {"58040b2c6de2e840": 1376952627}
+TWO_STEP_TRAFFIC = {"beb44d070954240c": 1376892211}
 KERNEL_SOURCES = ["lbm_device.hpp", "lbm_kernels.hpp", "lbm_params.hpp", "lbm_launch.hpp", "lbm_two_step.hpp",
                   "lbm_q19_f32.hip", "sweep_plan.hpp"]
 
