@@ -26,9 +26,9 @@
 // with waves that hold ring columns only skipping stage 2 135 us.  The ring
 // and the two extra planes of a chunk are collided by more than one workgroup;
 // their reads mostly hit the L2.  rD3Q27 FP32 256 x 256 x 128: 293 -> 192 us a
-// step; rD3Q19 FP64: 449 -> 303 us.  FP16 storage gained nothing (106 -> 111 us:
-// as many instructions for half the bytes) and rD3Q27 FP64 lost (its rows of
-// 27 doubles leave patches of 512 columns), so neither is built.
+// step; rD3Q19 FP64: 449 -> 303 us.  FP16 storage in the patches of FP32 gained
+// nothing (106 -> 111 us; patches sized for its entries are not tried) and rD3Q27
+// FP64 lost (its rows of 27 doubles leave patches of 512 columns), so neither is built.
 //
 // The arithmetic is the single step's (collide_nse, and the storage type
 // between the steps), so the results are those of two single steps bit for

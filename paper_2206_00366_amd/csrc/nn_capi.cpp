@@ -12,6 +12,7 @@ namespace nn {
 hipError_t launch_conv(const uint16_t*, const uint16_t*, const float*, float*, uint16_t*, const float*, int, int, int,
                        int, int, int, int, hipStream_t);
 hipError_t launch_flip(const uint16_t*, uint16_t*, int, int, hipStream_t);
+size_t wgrad_need_floats(int, int, int, int, int);
 size_t wgrad_scratch_floats(int, int, int, int, int);
 hipError_t launch_wgrad(const uint16_t*, const uint16_t*, int, int, int, int, int, int, float*, float*, float*, size_t,
                         hipStream_t);
@@ -80,7 +81,7 @@ int rmrt_nn_conv_backward_weight(const void* x, const void* dy, int B, int H, in
   if (!x || !dy || !dw || !scratch) return nn_fail(RMRT_EINVAL, "NULL pointer");
   if (!ch_ok(Cin) || !ch_ok(Cout)) return nn_fail(RMRT_EUNSUPPORTED, "channels must be 16 or 32");
   if (B < 1 || H < 1 || W < 1) return nn_fail(RMRT_EINVAL, "bad sizes");
-  if (scratch_floats < rmrt_nn_wgrad_scratch_floats(B, H, W, Cin, Cout))
+  if (scratch_floats < wgrad_need_floats(B, H, W, Cin, Cout))
     return nn_fail(RMRT_EINVAL, "scratch too small");
   return hip_rc(launch_wgrad((const uint16_t*)x, (const uint16_t*)dy, B, H, W, Cin, Cout, dil, dw, db, scratch,
                              scratch_floats, (hipStream_t)stream),

@@ -577,8 +577,12 @@ static long wgrad_blocks(int B, int H, int W, long* per_block) {
 static size_t wgrad_partial_floats(long blocks, int Cin, int Cout) {
   return (size_t)blocks * (4 / ((Cin / 16) * (Cout / 16))) * ((size_t)9 * Cin * Cout + Cout);
 }
-// Scratch for these sizes and all smaller ones (an even share can need fewer
-// workgroups for more segments: 257 for 513, 512 for 512).
+// Scratch of a launch, and scratch for these sizes and all smaller ones (an even
+// share can need fewer workgroups for more segments: 257 for 513, 512 for 512).
+size_t wgrad_need_floats(int B, int H, int W, int Cin, int Cout) {
+  long per = 0;
+  return wgrad_partial_floats(wgrad_blocks(B, H, W, &per), Cin, Cout);
+}
 size_t wgrad_scratch_floats(int B, int H, int W, int Cin, int Cout) {
   const long items = wgrad_items(B, H, W);
   return wgrad_partial_floats(items < kWgBlocks ? items : kWgBlocks, Cin, Cout);

@@ -84,3 +84,12 @@ def test_narrow_images_take_about_the_time_of_wide_ones(R, W):
         scr = torch.empty(R.nn_wgrad_scratch_floats(16, 8192 // w, w, 32, 32), device="cuda")
         times.append(seconds(lambda: R.nn_conv_backward_weight(x, dy, 1, dw, db, scr)))
     assert times[0] < 2.0 * times[1], times
+
+
+def test_scratch_of_exactly_a_launch_s_need_is_enough(R):
+    """513 row segments take 257 workgroups; what the report asks for also serves smaller images."""
+    x, dy = (torch.randn(1, 513, 128, 32, device="cuda").bfloat16() for _ in range(2))
+    want, got = (torch.empty(32, 3, 3, 32, device="cuda") for _ in range(2))
+    R.nn_conv_backward_weight(x, dy, 1, want, None, torch.empty(R.nn_wgrad_scratch_floats(1, 513, 128, 32, 32), device="cuda"))
+    R.nn_conv_backward_weight(x, dy, 1, got, None, torch.empty(257 * (9 * 32 * 32 + 32), device="cuda"))
+    assert torch.equal(want, got)

@@ -18,3 +18,14 @@ def test_smaller_images_need_no_more_scratch(channels):
     for B, H, W in ((16, 64, 128), (3, 171, 100), (9, 57, 260)):
         top = need(B, H, W, *channels)
         assert all(need(b, h, w, *channels) <= top for b in (1, B) for h in (1, H // 2, H) for w in (1, W // 3, W))
+
+
+def test_scratch_is_refused_below_what_a_launch_needs():
+    """513 row segments are shared by 257 workgroups: their slots are enough, a float less
+    is refused before anything is launched (no GPU: the pointers are never used)."""
+    import ctypes as C
+    p = C.c_void_p(16)
+    slots = 257 * (9 * 32 * 32 + 32)
+    code = rmrt.lib().rmrt_nn_conv_backward_weight(p, p, 1, 513, 128, 32, 32, 1, p, None, p, slots - 1, None)
+    assert code == rmrt.EINVAL and b"scratch" in rmrt.lib().rmrt_last_error()
+    assert rmrt.nn_wgrad_scratch_floats(1, 513, 128, 32, 32) == 512 * (9 * 32 * 32 + 32)
