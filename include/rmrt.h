@@ -284,7 +284,8 @@ int rmrt_set_source_fields(rmrt_ctx* ctx, const void* S, const void* F, void* st
  * (raw-moment NSE, or NCDE without c_zero; FP32, or FP64 without force and
  * source; walls on both of two opposite faces or none; solid masks) take four
  * steps or more as passes of two to four steps each on the same terms, in the
- * lengths that are faster than single steps.
+ * lengths that are faster than single steps; their second buffer comes with the
+ * first call that takes passes.
  */
 int rmrt_step(rmrt_ctx* ctx, int nsteps, void* stream);
 

@@ -1086,8 +1086,9 @@ int send_second(rmrt_ctx* c, Item* items, size_t nitems, hipStream_t s) {
   return send_pass_memory(c->staged, in_place ? 1 : 0, c->ddoms + c->dom, items, nitems, s);
 }
 
-// The tile path of an rD2Q9 context, set up on its first call of four steps or more.
-int tile_prepare(rmrt_ctx* c, hipStream_t s) {
+// The tile path of an rD2Q9 context, set up on its first call whose m (even) steps
+// take passes.
+int tile_prepare(rmrt_ctx* c, int m, hipStream_t s) {
   if (c->batch || !tile_model(c, step_eq(c), step_force(c))) return RMRT_OK;
   c->two_step = -1;
   std::vector<TileItem> items;
@@ -1097,6 +1098,10 @@ int tile_prepare(rmrt_ctx* c, hipStream_t s) {
     return RMRT_OK;
   }
   if (items.empty()) return RMRT_OK;
+  if (tile_call(c->tile_rule, m).passes() == 0) {
+    c->two_step = 0;   // not for this call: asked again for others
+    return RMRT_OK;
+  }
   const bool in_place = c->p.pattern == RMRT_AA;
   const size_t second_bytes = in_place ? (size_t)9 * c->hdom.ld * elem_size(c->p.storage) : 0;
   if (!pass_memory(items, second_bytes, in_place ? 1 : 0, &c->tile_items, &c->second, &c->staged)) return RMRT_OK;
@@ -1119,12 +1124,12 @@ int launch_tile_passes(StepLaunch a, int lattice, int storage, bool ab, const Ti
   return RMRT_OK;
 }
 
-// Set up the two-step path of a context on its first call of four steps or
-// more.  A domain it does not serve, or memory that is not there, leaves the
-// single steps.
-int two_step_prepare(rmrt_ctx* c, hipStream_t s) {
-  if (c->launch_set || c->two_step != 0) return RMRT_OK;   // (single steps only: asked again after rmrt_tune)
-  if (c->p.lattice == RMRT_Q9) return tile_prepare(c, s);
+// Set up the multi-step path of a context on its first call of four steps or
+// more (rD2Q9: the first that takes passes).  A domain it does not serve, or
+// memory that is not there, leaves the single steps.
+int two_step_prepare(rmrt_ctx* c, int n, long long first, hipStream_t s) {
+  if (n < 4 || c->launch_set || c->two_step != 0) return RMRT_OK;   // (launch_set: asked again after rmrt_tune)
+  if (c->p.lattice == RMRT_Q9) return tile_prepare(c, (n - (c->p.pattern != RMRT_AB && (first & 1) ? 1 : 0)) & ~1, s);
   if (!two_step_model(c)) return RMRT_OK;   // asked again: source fields may be detached later
   c->two_step = -1;
   const int q = lattice_q(c->p.lattice), es = (int)elem_size(c->p.storage);
@@ -1229,7 +1234,7 @@ int graph_for(rmrt_ctx* c, int n, long long first, hipGraphExec_t* out, hipStrea
   auto it = c->graphs.find(key);
   if (it == c->graphs.end()) {
     const int paths = c->two_step;
-    int rc = n >= 4 ? two_step_prepare(c, stream) : RMRT_OK;
+    int rc = two_step_prepare(c, n, first, stream);
     if (rc != RMRT_OK) return rc;
     // a preparing call may be followed by steps on another stream
     if (upload && c->two_step != paths) HIP_TRY(hipStreamSynchronize(stream));
@@ -2239,10 +2244,11 @@ void batch_advance(rmrt_batch* b, int n) {
   for (auto* c : b->ctxs) c->steps = b->steps;
 }
 
-// The tile path of a batch of rD2Q9 domains, set up on its first call of four
-// steps or more.
-int batch_tile_prepare(rmrt_batch* b, hipStream_t s) {
-  if (b->shape_set || b->tile_steps != 0) return RMRT_OK;   // (single steps only: asked again after the autotuner)
+// The tile path of a batch of rD2Q9 domains, set up on its first call that takes
+// passes.
+int batch_tile_prepare(rmrt_batch* b, int n, long long first, hipStream_t s) {
+  const int m = (n - (b->pattern != RMRT_AB && (first & 1) ? 1 : 0)) & ~1;
+  if (m < 4 || b->shape_set || b->tile_steps != 0) return RMRT_OK;   // (shape_set: asked again after the autotuner)
   b->tile_steps = -1;
   size_t bytes = 0;
   for (const rmrt_ctx* c : b->ctxs) {
@@ -2256,6 +2262,10 @@ int batch_tile_prepare(rmrt_batch* b, hipStream_t s) {
     return RMRT_OK;
   }
   if (items.empty()) return RMRT_OK;
+  if (tile_call(b->tile_rule, m).passes() == 0) {
+    b->tile_steps = 0;   // not for this call: asked again for others
+    return RMRT_OK;
+  }
   const bool in_place = b->pattern == RMRT_AA;
   const size_t nblocks = in_place ? b->ctxs.size() : 0;
   if (!pass_memory(items, in_place ? bytes : 0, nblocks, &b->tile_items, &b->second, &b->staged)) return RMRT_OK;
@@ -2318,7 +2328,7 @@ int batch_graph_for(rmrt_batch* b, int n, long long first, hipGraphExec_t* out, 
   auto it = b->graphs.find(key);
   if (it == b->graphs.end()) {
     const int paths = b->tile_steps;
-    int rc = n >= 4 ? batch_tile_prepare(b, stream) : RMRT_OK;
+    int rc = batch_tile_prepare(b, n, first, stream);
     if (rc != RMRT_OK) return rc;
     if (upload && b->tile_steps != paths) HIP_TRY(hipStreamSynchronize(stream));
     if (!b->cap) HIP_TRY(hipStreamCreateWithFlags(&b->cap, hipStreamNonBlocking));

@@ -271,12 +271,33 @@ static void counted_launches() {
       }
 }
 
+// A call on rD2Q9 that takes no passes sets none up; a later one that does finds them.
+static void only_for_passes() {
+  const Form wide[] = {
+      {"tiles AA, wide", RMRT_Q9, RMRT_F32DEV, RMRT_AA, 1500, 700, 1, 0},
+      {"tiles AB, wide", RMRT_Q9, RMRT_F64, RMRT_AB, 1024, 512, 1, 0},
+      {"batch AA, wide", RMRT_Q9, RMRT_F32DEV, RMRT_AA, 1500, 1024, 1, 3},
+      forms[1], forms[5],
+  };
+  for (const Form& fm : wide) {
+    const std::string where = fm.name;
+    Runner r(fm);
+    CHECK(r.step(1) == RMRT_OK);   // calls of four steps from an odd one: three from an even one
+    for (int n : {2, 3, 4, 5, 4}) {
+      const size_t before = live_bytes;
+      CHECK(r.passes(n) || live_bytes == before);
+    }
+    CHECK(r.passes(24));
+  }
+}
+
 int main(int argc, char** argv) {
   const std::string s = argc > 1 ? argv[1] : "";
   if (s == "out_of_memory") out_of_memory();
   else if (s == "no_wait") no_wait();
   else if (s == "failed_tuning") failed_tuning();
   else if (s == "counted_launches") counted_launches();
+  else if (s == "only_for_passes") only_for_passes();
   else return fprintf(stderr, "unknown scenario\n"), 1;
   printf("ok\n");
   return 0;

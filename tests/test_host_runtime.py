@@ -50,3 +50,7 @@ def test_failed_tuning_leaves_the_path_as_it_was(driver):
 
 def test_reported_launches_are_the_ones_made(driver):
     run(driver, "counted_launches")
+
+
+def test_calls_without_passes_set_none_up(driver):
+    run(driver, "only_for_passes")
